@@ -237,10 +237,8 @@ lmbp_status linear_swiglu_fwd(lmbp_dtype dt, int64_t m, int64_t n, int64_t k, co
  *                                      rounding (equal to z W^T + b in exact arithmetic;
  *                                      not byte-equal to linear_act_fwd applied to z).
  *
- * One statistics pass over x writes rstd; then the GEMM runs on x, and after their K
- * loops its blocks also write z (each row tile's columns shared out among the blocks of
- * that row, x read again from the caches), so the norm's output traffic overlaps the
- * matrix products of other blocks.
+ * The norm kernel writes z and rstd; then the GEMM runs on x and applies rstd to each
+ * row's sums in its epilogue.
  *
  *   dt   : LMBP_BF16 only.
  *   m,n,k, x, w, bias, y, codes : as linear_act_fwd, with k >= 8 when m > 0.

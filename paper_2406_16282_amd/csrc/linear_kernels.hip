@@ -1,7 +1,7 @@
 // Linear layer with a fused ReGELU2 / ReSiLU2 forward epilogue, for gfx950.
 //
 // z = x W^T (+ b): x [M x K] and W [N x K] (the weight of a linear layer) are bf16
-// and K-contiguous; products accumulate in fp32 on v_mfma_f32_32x32x16_bf16 and z is
+// and K-contiguous; products accumulate in fp32 on v_mfma_f32_16x16x32_bf16 and z is
 // rounded once to bf16 (bias added in fp32 before the rounding). The epilogue then
 // applies the activation to the rounded z and stores y = act(z) and the 2-bit codes
 // of z (Sec. 4.2; 16 codes per word over the flattened [M x N] output), i.e. exactly
@@ -9,38 +9,60 @@
 // the caller asks for it: ReGELU2 / ReSiLU2 keep only the codes for the backward
 // pass, so the pre-activation never has to reach HBM.
 //
-// Tiling. A block computes a BM x BN tile of z with WM x WN waves, each a
-// (BM/WM) x (BN/WN) part as 32 x 32 MFMA tiles, accumulators in registers. Two tile
-// configurations are compiled and chosen per problem (launcher): 256 x 256 with 8 waves
-// of 128 x 64 for large problems, 128 x 128 with 8 waves of 64 x 32 (two blocks per CU)
-// when the large tiles would leave much of the last round of the GPU idle.
+// What bounds it. Large products: the card's power. With random operands a loop of
+// nothing but 32x32x16 MFMAs runs at 1840 TFLOP/s and of 16x16x32 ones at 2085 (2440 for
+// both on zeros), so the smaller shape is used although it needs as many operand reads:
+// the [8192 x 4096] x [4096 x 11008] SiLU layer took 641 us before and 606 us after that
+// change alone, with the same bits. Then the delivery of operands: with one block
+// barrier per K step and all of a step's loads issued behind it, the matrix cores were
+// busy 70% of the cycles; the ring below (half steps, loads spread over the MFMAs, two
+// to three half steps in flight) gave 597 us, the persistent blocks with the epilogue in
+// registers 581 us; the gated [8192 x 4096] x 2 [4096 x 11008] layer went from 1213 to
+// 1113 us. Products with a short K (ViT-B: 768): the epilogue, about 22 VALU operations
+// per element, is as long as the K loop; two blocks per CU let one block's epilogue run
+// beside the other's MFMAs (78 us, against 83-86 us for either of the other tiles).
 //
-// K loop. K advances in steps of BK = 64 (32 also compiles) through a ring of LDS stages
-// (two for the shipped configurations) filled straight from HBM by raw buffer loads
-// with an LDS destination (buffer_load_dwordx4 ... lds), so no register staging is
-// needed; the longer step halves the block barriers per flop, which is what the matrix
-// cores were waiting on. The buffer resources end at the tile's last valid row, so
-// ragged tiles read zeros without branches, and chunks beyond K are pointed past the end
-// to read zeros too. A stage row is BK bf16 = U = BK / 8 sixteen-byte units, unit u of
-// row r holding k-chunk u ^ ((r >> s) % U), with 2^s rows per 256 bytes, so that the
-// operand reads of 16 consecutive rows at one k-chunk hit distinct LDS banks; one load
-// instruction of a wave fills 1 KiB (64 / U rows), lane l writing unit l % U of row
-// l / U (the row's U lanes read its 2 BK contiguous bytes in permuted order). Within the loop the fragments of the next K slice (16) are read into
-// their own registers while the MFMAs of the current one run (scheduling groups put one
-// MFMA between consecutive loads and reads), across step boundaries too; the loop body
-// is branch-free (loads past the last step read zeros into spent
-// buffers) so that the compiler's LDS waits are exact. Lane layout of the MFMA (checked
-// on the hardware): lane l supplies row l % 32 of A and column l % 32 of B at
-// k = 8 (l / 32) .. + 7, and holds result rows 8 (r / 4) + 4 (l / 32) + r % 4 of column
-// l % 32 in accumulator register r.
+// Tiling. A block computes a BM x BN tile of z with WM x WN waves, each BM/WM x 64 as
+// 16 x 16 MFMA tiles, accumulators in registers. Four tiles are compiled; the launcher
+// picks one by a cost model of the measured times (below).
 //
-// Epilogue: the tile (bias added, rounded to bf16) is written to LDS and read back so
-// that each thread owns 16 consecutive columns of a row: two 16-byte stores of y (and
-// of z), one code word, the same arithmetic as the activation kernels' fast path.
+// K loop. K advances in steps of 64, each in two half steps. The LDS is a ring of slots
+// of half a step's operands: slot 2t holds the first half of every wave's rows of x and
+// of its rows of W (all 64 k), slot 2t + 1 the second halves. A half step h computes the
+// products of fragments already in registers, reads the fragments that the next ones
+// need from slot h + 1, and issues the loads of slot h + kRing into the place of slot h,
+// whose last reader passed the barrier before. One barrier per half step, and a wait
+// that leaves kRing - 2 slots of loads in flight (loads return in order; any other
+// vector-memory operation in between only makes the wait stricter). The slots are filled
+// straight from memory by raw buffer loads with an LDS destination. The buffer resources
+// end at the tile's last valid row, so ragged tiles read zeros without branches, and
+// chunks beyond K are pointed past the end to read zeros too. An LDS row is 64 bf16 =
+// eight 16-byte units; unit u of row r holds k-chunk u ^ swz(r), with swz chosen so that
+// the 16 rows of an operand read at one k-chunk fall into distinct banks: (r >> 1) % 8
+// for x (rows 16 apart in a read: r = 16 i + 0 .. 15), bit 1 and bits 3..4 of r for W
+// (rows 8 a + 4 j + 0 .. 3, a = 0 .. 3).
 //
-// Blocks are mapped to tiles XCD by XCD (the hardware deals consecutive blocks out
-// to the 8 XCDs in turn), in groups of 8 row tiles, so that the blocks sharing an XCD's
-// L2 also share their x and W tiles.
+// Blocks are persistent (as many as fit the device) and the stream of loads runs on from
+// one tile into the next: the first K steps of the next tile are under way while the
+// epilogue of the current one runs. Tiles are dealt out XCD by XCD (consecutive blocks
+// go to the 8 XCDs in turn) in groups of 8 row tiles, so that the blocks sharing an
+// XCD's L2 also share their x and W tiles.
+//
+// Epilogue, in registers. The MFMA takes W rows as its first operand, so lane l holds
+// row l % 16 of a 16-row block and, in register r of tile j, W index p = 4 (l / 16) + r.
+// The rows of W are dealt to the tiles such that p of tile j is output column
+// 16 (p / 4) + 4 j + p % 4 of the wave's 64: a lane holds 16 consecutive columns, one
+// whole code word and 32 bytes of y. Gated form: the first half of a wave's W rows comes
+// from the gate weight, the second from the up weight, for the same 32 output columns; a
+// lane holds 8 consecutive columns of both, and two lanes make a code word. Lane layout
+// of the MFMA (checked on the hardware): lane l supplies row l % 16 of the first operand
+// and column l % 16 of the second at k = 8 (l / 16) .. + 7, and holds result rows
+// 4 (l / 16) + 0 .. 3 of column l % 16.
+//
+// Norm in front (MS-RMSNorm, Sec. 5.2): the norm kernel writes z and rstd first, and this
+// kernel multiplies each row's fp32 sums by its rstd (with the bias, one fused
+// multiply-add). Letting the GEMM write z instead saved the norm kernel's stores but
+// stretched the epilogue by more: [2048 x 4096] with two 11008-row weights, 415 us then.
 #include "lmbp_device.hpp"
 #include "act_codes.hpp"
 #include "act_math.hpp"
@@ -52,72 +74,62 @@ namespace lmbp {
 namespace lin {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 constexpr uint32_t kBufferGDword3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
 constexpr uint32_t kOutOfRange = 0x80000000u;    // beyond any resource's range: reads 0
+constexpr int kBK = 64;                          // K step: an LDS row is 128 bytes
 
-template <int BM_, int BN_, int WM_, int WN_, int STAGES_ = 4, int BK_ = 32>
+// MINW: waves per SIMD that the registers are budgeted for (blocks per CU follow from it).
+template <int BM_, int BN_, int WM_, int WN_, int MINW_, int RING_ = 4>
 struct Tile {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-  static constexpr int kStages = STAGES_;   // LDS ring
-  static constexpr int BK = BK_;            // K step: a stage row is 2 BK bytes
-  static constexpr int kSlices = BK / 16;   // MFMA K slices per step
-  static constexpr int kUnits = BK / 8;     // 16-byte units per stage row
-  static constexpr int kRowsPerLoad = 64 / kUnits;            // rows one 1 KiB load fills
-  static constexpr int kSwzShift = BK == 32 ? 2 : 1;          // rows per 256 bytes: 4 or 2
-  static_assert(BK == 32 || BK == 64, "K step of 32 or 64");
-  static constexpr int kWaves = WM * WN;
-  static constexpr int kThreads = kWaves * kWave;
-  static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;   // MFMA tiles per wave
-  static constexpr int kStageElems = (BM + BN) * BK;
-  static constexpr int kEpiRow = BN + 8;                        // padded epilogue row
-  static constexpr int kOperandElems = kStages * kStageElems;
-  static constexpr int kLdsElems =
-      (kOperandElems > BM * kEpiRow) ? kOperandElems : BM * kEpiRow;
-  static constexpr int kLdsElemsNorm = kLdsElems + 2 * BM;   // + the rows' rstd (fp32)
-  static constexpr int kLA = BM / kRowsPerLoad / kWaves, kLB = BN / kRowsPerLoad / kWaves;
-  static constexpr int kLoadsPerStage = kLA + kLB;
-  static constexpr int kEpiThreadsPerRow = BN / 16;
-  static constexpr int kEpiRowStep = kThreads / kEpiThreadsPerRow;
-  static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0, "wave tiles are multiples of 32");
-  static_assert((BM / kRowsPerLoad) % kWaves == 0 && (BN / kRowsPerLoad) % kWaves == 0,
-                "load blocks per wave");
-  static_assert(kThreads % kEpiThreadsPerRow == 0, "epilogue mapping");
-  static_assert(kLdsElemsNorm * 2 <= 160 * 1024, "LDS per block");
-  static_assert(kStages >= 2 && (kStages - 1) * kLoadsPerStage <= 63, "vector-memory counter range");
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, kMinWaves = MINW_;
+  static constexpr int kWaves = WM * WN, kThreads = kWaves * kWave;
+  static constexpr int HM = BM / WM / 2, HN = 32;       // half of a wave's rows, columns
+  static constexpr int TMH = HM / 16, TNH = HN / 16;    // MFMA tiles per half
+  static constexpr int TM = 2 * TMH, TN = 2 * TNH;
+  static constexpr int kSlotElems = (BM + BN) / 2 * kBK;   // one ring slot: half of A and of B
+  static constexpr int kRing = RING_;                   // slots in LDS
+  static constexpr int kBlocksPerCu = kMinWaves * 4 / kWaves;
+  static constexpr int kLA = BM / 16 / kWaves, kLB = BN / 16 / kWaves;   // 1 KiB loads per wave
+  static constexpr int kSideBytes = 4 * (BN * 2 + BM * 4);   // bias and rstd of four tiles
+  static constexpr int kLdsBytes = kRing * kSlotElems * 2 + kSideBytes;
+  static_assert(BN / WN == 64 && HM % 16 == 0, "wave tile");
+  static_assert(kLA >= 1 && kLB >= 1 && (BM / 16) % kWaves == 0 && (BN / 16) % kWaves == 0, "loads");
+  static_assert(kLdsBytes * kBlocksPerCu <= 160 * 1024, "LDS per CU");
 };
 
-#ifndef LMBP_LIN_SMALL
-#define LMBP_LIN_SMALL 128, 128, 2, 4, 2, 64   // the same for the small configuration (8 waves)
-#endif
-#ifndef LMBP_LIN_BIG
-#define LMBP_LIN_BIG 256, 256, 2, 4, 2, 64   // BM, BN, WM, WN, stages, K step: large configuration
-#endif
-using BigTile = Tile<LMBP_LIN_BIG>;
-using SmallTile = Tile<LMBP_LIN_SMALL>;
+using BigTile = Tile<256, 256, 2, 4, 2>;      // one block of 8 waves per CU
+using MidTile = Tile<128, 256, 1, 4, 2, 3>;   // two blocks of 4 waves
+using SmallTile = Tile<128, 128, 4, 2, 4>;    // two blocks of 8 waves
+using LowTile = Tile<64, 128, 2, 2, 3>;       // three blocks of 4 waves
+
+// The grid of tiles: sizes, tiles per XCD, and floor(2^32 / tiles_n).
+struct TileMap {
+  uint32_t tiles_m, tiles_n, tiles, per_xcd, inv_n;
+};
 
 // The target builtins below are wrapped in device functions: used directly in the body of
 // a kernel template, they make the host-side instantiation fail silently and the launch
 // stub is never emitted.
 
 // A raw buffer resource over `bytes` bytes at `base` (reads beyond return zeros).
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const uint16_t* base, int64_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, int(bytes),
-                                           kBufferGDword3);
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kBufferGDword3);
 }
-
-// 16 bytes per lane from the buffer into LDS at `dst` + lane * 16 (dst wave-uniform).
-__device__ inline void load_lds16(__amdgpu_buffer_rsrc_t r, uint16_t* dst, uint32_t offset) {
+// 16 or 4 bytes per lane from the buffer into LDS at `dst` + lane * 16 or 4 (dst wave-uniform).
+__device__ inline void load_lds16(__amdgpu_buffer_rsrc_t r, void* dst, uint32_t offset) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, offset, 0, 0, 0);
 }
+__device__ inline void load_lds4(__amdgpu_buffer_rsrc_t r, void* dst, uint32_t offset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 4, offset, 0, 0, 0);
+}
 
-// Scheduling groups for one K slice: its MF MFMAs, with VM buffer loads and then DS LDS
-// reads spread over the first half of them (so the reads have landed before the slice
-// ends and the next wait finds nothing outstanding).
+// Scheduling groups for MF MFMAs, with VM buffer loads and then DS LDS reads spread over
+// the first half of them (so the reads have landed before the next wait).
 template <int MF, int VM, int DS, int I = 0>
 __device__ inline void spread() {
   if constexpr (I < MF) {
@@ -133,23 +145,33 @@ __device__ inline void spread() {
   }
 }
 
-// Tile coordinates of this block (see the file comment).
-__device__ inline void block_tile(int64_t tiles_m, int64_t tiles_n, int64_t& tm, int64_t& tn) {
-  const int64_t nblk = tiles_m * tiles_n;
-  const int64_t b = blockIdx.x;
-  const int64_t per = nblk / kXcds;
-  const int64_t id = (b < per * kXcds) ? (b % kXcds) * per + b / kXcds : b;
-  const int64_t in_group = kGroupM * tiles_n;
-  const int64_t first_m = (id / in_group) * kGroupM;
-  const int64_t gsize = (tiles_m - first_m < kGroupM) ? tiles_m - first_m : kGroupM;
-  const int64_t r = id % in_group;
-  tm = first_m + r % gsize;
-  tn = r / gsize;
+// Tile coordinates of the t-th tile (see the file comment). tiles_n is divided by with a
+// host-made reciprocal (floor(2^32 / tiles_n), at most one short of the quotient for
+// t < 2^30) instead of an integer division.
+__device__ inline void tile_of(uint32_t t, const TileMap& m, uint32_t& tm, uint32_t& tn) {
+  const uint32_t id = (t < m.per_xcd * kXcds) ? (t % kXcds) * m.per_xcd + t / kXcds : t;
+  const uint32_t id8 = id / kGroupM;
+  uint32_t group = __umulhi(id8, m.inv_n);
+  uint32_t in = id8 - group * m.tiles_n;
+  while (in >= m.tiles_n) {
+    in -= m.tiles_n;
+    ++group;
+  }
+  const uint32_t first_m = group * kGroupM, r = in * kGroupM + id % kGroupM;
+  const uint32_t left = m.tiles_m - first_m;
+  if (left >= uint32_t(kGroupM)) {
+    tm = first_m + r % kGroupM;
+    tn = r / kGroupM;
+  } else {   // the last, smaller group of row tiles
+    tm = first_m + r % left;
+    tn = r / left;
+  }
 }
 
 // Arguments of the kernel (by value). Plain form: y = act(z), z = x w^T + bias.
 // Gated form (GLU): g = x w^T and u = x w2^T (no bias), y = h = act(g) * u, s = act(g),
-// u stored; z (optional) receives g; codes are those of g.
+// u stored; z (optional) receives g; codes are those of g. Norm in front (NORM): x is the
+// norm's input and rstd its per-row statistic.
 struct LinArgs {
   const uint16_t* x;
   const uint16_t* w;
@@ -161,384 +183,405 @@ struct LinArgs {
   uint32_t* codes;
   uint16_t* z;
   int64_t M, N, K;
-  // Norm in front (NORM): x is the norm's input, rstd its per-row statistic (fp32), and
-  // zn [M x K] receives the norm's output z = bf16(x rstd).
   const float* rstd;
-  uint16_t* zn;
+  TileMap map;
 };
 
 template <class C, int ACT, bool GLU, bool NORM>
-__global__ __launch_bounds__(C::kThreads) void linear_act_fwd_kernel(LinArgs a) {
+__global__ __launch_bounds__(C::kThreads, C::kMinWaves) void linear_act_fwd_kernel(LinArgs a) {
   using A = ActOf<ACT>;
-  constexpr int BM = C::BM, BN = C::BN, TM = C::TM, TN = C::TN, kWaves = C::kWaves;
-  // Output columns per block: the gated form spends half of the B tile on each weight.
+  constexpr int BM = C::BM, BN = C::BN, TM = C::TM, TN = C::TN, TMH = C::TMH, TNH = C::TNH;
+  constexpr int HM = C::HM, HN = C::HN, kWaves = C::kWaves;
+  constexpr int kLA = C::kLA, kLB = C::kLB, kL = kLA + kLB;
   constexpr int kOut = GLU ? BN / 2 : BN;
-  static_assert(!GLU || C::kLB % 2 == 0, "gated form: each weight fills half the B loads");
-  const uint16_t* __restrict__ x = a.x;
-  const uint16_t* __restrict__ w = a.w;
+  constexpr int kSlot = C::kSlotElems;
   const int64_t M = a.M, N = a.N, K = a.K;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
+  uint16_t* const bias_lds = lds + C::kRing * kSlot;
+  float* const rstd_lds = reinterpret_cast<float*>(bias_lds + 4 * BN);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = wave_in_block();
   const int wm = wave / C::WN, wn = wave % C::WN;
+  const uint32_t tiles = a.map.tiles;
+  const int kt_count = K > 0 ? int((K + kBK - 1) / kBK) : 1;
 
-  int64_t tm, tn;
-  const int64_t tiles_n = (N + kOut - 1) / kOut;
-  block_tile((M + BM - 1) / BM, tiles_n, tm, tn);
-  const int64_t m0 = tm * BM, n0 = tn * kOut;
+  // The bias goes through LDS in 4-byte loads; one that starts between two words is read
+  // in the epilogue instead.
+  const bool bias_staged = a.bias != nullptr && (reinterpret_cast<uintptr_t>(a.bias) & 2) == 0;
 
-  // Norm in front: the block's rows' rstd in LDS past the operand / epilogue area
-  // (visible after the first barrier).
-  float* rs_lds = reinterpret_cast<float*>(lds + C::kLdsElems);
-  if constexpr (NORM) {
-    for (int r = tid; r < BM; r += C::kThreads) rs_lds[r] = (m0 + r < M) ? a.rstd[m0 + r] : 0.0f;
+  // ---- load side: byte offsets of this lane's chunks at K step 0, for both halves
+  uint32_t ld_a[2][kLA], ld_b[GLU ? 1 : 2][kLB];
+  int kc_a[kLA], kc_b[kLB];
+  const int r_in = lane / 8, u_in = lane % 8;
+#pragma unroll
+  for (int q = 0; q < kLA; ++q) {
+    const int lr = (wave + kWaves * q) * 8 + r_in;
+    kc_a[q] = (u_in ^ ((lr >> 1) & 7)) * 8;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      ld_a[h][q] = uint32_t(((lr / HM) * 2 * HM + h * HM + lr % HM) * K * 2 + kc_a[q] * 2);
   }
-
-  f32x16 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int q = 0; q < kLB; ++q) {
+    const int lr = (wave + kWaves * q) * 8 + r_in;
+    kc_b[q] = (u_in ^ (((lr >> 1) & 1) | (((lr >> 3) & 3) << 1))) * 8;
+    if constexpr (GLU) {
+      ld_b[0][q] = uint32_t(lr * K * 2 + kc_b[q] * 2);
+    } else {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-  // Buffer resources over the block's rows of x and W.
-  const int64_t rows_x = (M - m0 < BM) ? M - m0 : BM;
-  const int64_t rows_w = (N - n0 < kOut) ? N - n0 : kOut;
-  const auto rx = make_rsrc(x + m0 * K, rows_x * K * 2);
-  const auto rw = make_rsrc(w + n0 * K, rows_w * K * 2);
-  const auto rw2 = make_rsrc(GLU ? a.w2 + n0 * K : w, GLU ? rows_w * K * 2 : 0);
-
-  // Loads: lane l of the wave's q-th 1 KiB block (stage rows R (wave + waves q) + l / U,
-  // R rows of U units) fetches k-chunk kc = (l % U) ^ swz(row) of its row, so that unit u
-  // of stage row r holds chunk u ^ swz(r), swz(r) = (r >> kSwzShift) % U.
-  const int r_in = lane / C::kUnits;
-  const int u_in = lane % C::kUnits;
-  auto chunk = [&](int stage_row) { return u_in ^ ((stage_row >> C::kSwzShift) & (C::kUnits - 1)); };
-  uint32_t ld_a[C::kLA], ld_b[C::kLB];  // byte offset of the chunk at K step 0
-  int kc_a[C::kLA], kc_b[C::kLB];
-#pragma unroll
-  for (int q = 0; q < C::kLA; ++q) {
-    const int row = (wave + kWaves * q) * C::kRowsPerLoad + r_in;
-    kc_a[q] = chunk(row);
-    ld_a[q] = uint32_t(row * K * 2 + kc_a[q] * 16);
+      for (int h = 0; h < 2; ++h)
+        ld_b[h][q] = uint32_t(((lr / 8) * 16 + h * 8 + lr % 8) * K * 2 + kc_b[q] * 2);
+    }
   }
-  // Gated form: B-tile rows below BN / 2 come from w, the others (the second half of the
-  // loads, q >= kLB / 2) from w2, each at its own row offset.
+  // Load cursor: tile l_tile (l_seq-th of this block), K step l_k. Past the last tile the
+  // resources are empty and the loads read zeros into slots that nothing reads.
+  uint32_t l_tile = blockIdx.x;
+  int l_seq = 0, l_k = 0;
+  __amdgpu_buffer_rsrc_t rx, rw, rw2;
+  auto enter_tile = [&]() {
+    uint32_t tm = 0, tn = 0;
+    const bool in = l_tile < tiles;
+    if (in) tile_of(l_tile, a.map, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * kOut;
+    const int64_t rows_x = !in ? 0 : (M - m0 < BM) ? M - m0 : BM;
+    const int64_t rows_w = !in ? 0 : (N - n0 < kOut) ? N - n0 : kOut;
+    rx = make_rsrc(a.x + m0 * K, rows_x * K * 2);
+    rw = make_rsrc(a.w + n0 * K, rows_w * K * 2);
+    if constexpr (GLU) rw2 = make_rsrc(a.w2 + n0 * K, rows_w * K * 2);
+    // The tile's bias and rstd, into one of four places: the cursor runs at most two tiles
+    // ahead of the tile being computed. Issued before the tile's first operands, they have
+    // landed when those have.
+    if constexpr (!GLU) {
+      if (bias_staged)
+        for (int v = wave; v < BN / 128; v += kWaves)
+          load_lds4(make_rsrc(a.bias + n0, rows_w * 2), bias_lds + (l_seq & 3) * BN + v * 128,
+                    uint32_t(v * 256 + lane * 4));
+    }
+    if constexpr (NORM) {
+      for (int v = wave; v < BM / 64; v += kWaves)
+        load_lds4(make_rsrc(a.rstd + m0, rows_x * 4), rstd_lds + (l_seq & 3) * BM + v * 64,
+                  uint32_t(v * 256 + lane * 4));
+    }
+  };
+  auto issue = [&](int h, uint16_t* S) {
+    const uint32_t k0 = uint32_t(l_k) * kBK;
 #pragma unroll
-  for (int q = 0; q < C::kLB; ++q) {
-    const int srow = (wave + kWaves * q) * C::kRowsPerLoad + r_in;
-    kc_b[q] = chunk(srow);
-    const int row = srow - ((GLU && q >= C::kLB / 2) ? BN / 2 : 0);
-    ld_b[q] = uint32_t(row * K * 2 + kc_b[q] * 16);
-  }
-  constexpr int kStages = C::kStages;
-  auto stage_ptr = [&](int64_t kt) { return lds + int(kt % kStages) * C::kStageElems; };
-  auto issue_stage = [&](int64_t kt) {
-    uint16_t* S = stage_ptr(kt);
-    const uint32_t k0b = uint32_t(kt * C::BK * 2);
+    for (int q = 0; q < kLA; ++q)
+      load_lds16(rx, S + (wave + kWaves * q) * 512, k0 + kc_a[q] < K ? ld_a[h][q] + k0 * 2 : kOutOfRange);
 #pragma unroll
-    for (int q = 0; q < C::kLA; ++q)
-      load_lds16(rx, S + (wave + kWaves * q) * 512,
-                 kt * C::BK + kc_a[q] * 8 < K ? ld_a[q] + k0b : kOutOfRange);
-#pragma unroll
-    for (int q = 0; q < C::kLB; ++q)
-      load_lds16((GLU && q >= C::kLB / 2) ? rw2 : rw, S + BM * C::BK + (wave + kWaves * q) * 512,
-                 kt * C::BK + kc_b[q] * 8 < K ? ld_b[q] + k0b : kOutOfRange);
+    for (int q = 0; q < kLB; ++q)
+      load_lds16((GLU && h == 1) ? rw2 : rw, S + BM / 2 * kBK + (wave + kWaves * q) * 512,
+                 k0 + kc_b[q] < K ? ld_b[GLU ? 0 : h][q] + k0 * 2 : kOutOfRange);
+  };
+  auto advance = [&]() {
+    if (++l_k == kt_count) {
+      l_k = 0;
+      l_tile += gridDim.x;
+      ++l_seq;
+      enter_tile();
+    }
   };
 
-  // Operand reads: lane l reads row (base + l % 32), k-chunk 2 kk + l / 32; wave rows
-  // start at multiples of 32, so the row's swizzle is ((l % 32) >> 2) & 3.
-  const int swz = ((lane & 31) >> C::kSwzShift) & (C::kUnits - 1);
-  int a_row[TM], b_row[TN];
+  // ---- compute side
+  const int a_off = (wm * HM + (lane & 15)) * kBK;
+  const int b_off = BM / 2 * kBK + (wn * HN + ((lane & 15) >> 2) * 8 + (lane & 3)) * kBK;
+  const int swa = (lane & 15) >> 1;
+  const int swb = ((lane >> 1) & 1) | (((lane >> 2) & 3) << 1);
+  const int ua[2] = {((lane >> 4) ^ swa) * 8, ((4 + (lane >> 4)) ^ swa) * 8};
+  const int ub[2] = {((lane >> 4) ^ swb) * 8, ((4 + (lane >> 4)) ^ swb) * 8};
+  bf16x8 fa[2][TMH][2], fb[2][TNH][2];
+  auto read_a = [&](const uint16_t* S, int h) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i) a_row[i] = (wm * TM * 32 + i * 32 + (lane & 31)) * C::BK;
+    for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-  for (int j = 0; j < TN; ++j) b_row[j] = BM * C::BK + (wn * TN * 32 + j * 32 + (lane & 31)) * C::BK;
-  bf16x8 fa[2][TM], fb[2][TN];
-  auto read = [&](const uint16_t* S, int kk, int buf) {
-    const int unit = ((2 * kk + (lane >> 5)) ^ swz) * 8;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(S + a_row[i] + unit);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const bf16x8*>(S + b_row[j] + unit);
+      for (int i = 0; i < TMH; ++i)
+        fa[h][i][kk] = *reinterpret_cast<const bf16x8*>(S + a_off + i * 16 * kBK + ua[kk]);
   };
-  auto mfmas = [&](int buf) {
+  auto read_b = [&](const uint16_t* S, int h) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int j = 0; j < TNH; ++j)
+        fb[h][j][kk] = *reinterpret_cast<const bf16x8*>(S + b_off + j * 4 * kBK + ub[kk]);
+  };
+  f32x4 acc[TM][TN];
+  auto quad = [&](int ha, int hb) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < TMH; ++i)
+#pragma unroll
+        for (int j = 0; j < TNH; ++j)
+          acc[ha * TMH + i][hb * TNH + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              fb[hb][j][kk], fa[ha][i][kk], acc[ha * TMH + i][hb * TNH + j], 0, 0, 0);
+  };
+  constexpr int MF = TMH * TNH * 2, RA = TMH * 2, RB = TNH * 2;
+
+  // An odd ring has its second-half slots loaded in first half steps and the other way round.
+  enter_tile();
+  constexpr int kRing = C::kRing;
+  constexpr bool kOdd = kRing % 2 != 0;
+#pragma unroll
+  for (int d = 0; d < kRing; ++d) {
+    issue(d & 1, lds + d * kSlot);
+    if (d & 1) advance();
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kRing - 2) * kL) : "memory");
+  asm volatile("s_barrier" ::: "memory");
+
+  int slot = 0;   // of the half step's first data unit
+  auto next = [&](int v, int d) { v += d; return v >= kRing ? v - kRing : v; };
+  int seq = 0;
+  for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x, ++seq) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
-  };
-
-  // Norm in front: the norm's output z = bf16(x rstd), stored with the norm kernel's
-  // rounding (fp32 product, round to nearest even). The x columns of K step kt of this
-  // row tile are written by the block with tn = kt mod tiles_n, from x read again (it
-  // has just streamed through the caches), outside the K loop, whose body stays
-  // branch-free. The block's first chunk is requested before the last K step's matrix
-  // products, which hide the loads. Consecutive lanes take consecutive 16-byte chunks of
-  // a row; rows beyond M and columns beyond K read through an empty range (zeros).
-  constexpr int kZv = NORM ? BM * (C::BK / 8) / C::kThreads : 1;
-  u32x4 zv[kZv];
-  auto z_chunk_load = [&](int64_t kt) {
-    constexpr int U = C::BK / 8;
-    const auto r = make_rsrc(x + m0 * K, rows_x * K * 2);
 #pragma unroll
-    for (int i = 0; i < kZv; ++i) {
-      const int q = tid + i * C::kThreads;
-      const int64_t col = kt * C::BK + (q % U) * 8;
-      zv[i] = __builtin_amdgcn_raw_buffer_load_b128(
-          r, col < K ? uint32_t(((q / U) * K + col) * 2) : kOutOfRange, 0, 0);
-    }
-  };
-  auto z_chunk_store = [&](int64_t kt) {
-    constexpr int U = C::BK / 8;
-#pragma unroll
-    for (int i = 0; i < kZv; ++i) {
-      const int q = tid + i * C::kThreads;
-      const int rr = q / U;
-      const int64_t col = kt * C::BK + (q % U) * 8;
-      if (m0 + rr < M && col < K) {
-        const float rsr = rs_lds[rr];
-        float f[8];
-        BF16::unpack(zv[i], f);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = f[e] * rsr;
-        *reinterpret_cast<u32x4*>(a.zn + (m0 + rr) * K + col) = BF16::pack(f);
-      }
-    }
-  };
-
-  // Loads of steps at or beyond the last one read zeros into buffers that are no longer
-  // needed, so every step sees the same number of loads in flight and the waits are
-  // constants (the vector-memory counter counts only these loads in the loop).
-  constexpr int kPendingFirst = (kStages - 1) * C::kLoadsPerStage;    // loads after step 0
-  constexpr int kPendingSteady = (kStages - 2) * C::kLoadsPerStage;   // after step kt + 1
-  const int64_t kt_count = (K + C::BK - 1) / C::BK;
-  if (kt_count > 0) {
-#pragma unroll
-    for (int s = 0; s < kStages; ++s) issue_stage(s);
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kPendingFirst) : "memory");
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+    // The tile's first fragments; no wave may load over them before all have read them.
+    read_a(lds + slot * kSlot, 0);
+    read_b(lds + slot * kSlot, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
-    read(stage_ptr(0), 0, 0);
-    for (int64_t kt = 0; kt + 1 < kt_count; ++kt) {
-      const uint16_t* S = stage_ptr(kt);
-#pragma unroll
-      for (int kk = 0; kk < C::kSlices; ++kk) {
-        if (kk + 1 < C::kSlices) {
-          read(S, kk + 1, (kk + 1) & 1);
-          mfmas(kk & 1);
-          spread<TM * TN, 0, TM + TN>();
-        } else {
-          // This wave's reads of step kt are complete once their data has arrived; after
-          // the barrier every wave's are, and step kt + 1 is in LDS.
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kPendingSteady) : "memory");
-          asm volatile("s_barrier" ::: "memory");
-          issue_stage(kt + kStages);   // into step kt's buffer
-          read(stage_ptr(kt + 1), 0, 0);
-          mfmas(kk & 1);
-          spread<TM * TN, C::kLoadsPerStage, TM + TN>();
-        }
-        __builtin_amdgcn_sched_barrier(0);   // the slice's MFMAs stay ahead of the next wait
-      }
-    }
-    const uint16_t* S = stage_ptr(kt_count - 1);
-    if constexpr (NORM) {
-      if (tn < kt_count) z_chunk_load(tn);
-    }
-#pragma unroll
-    for (int kk = 0; kk < C::kSlices; ++kk) {
-      if (kk + 1 < C::kSlices) read(S, kk + 1, (kk + 1) & 1);
+
+    for (int kt = 0; kt < kt_count; ++kt) {
+      uint16_t* S = lds + slot * kSlot;
+      uint16_t* S1 = lds + next(slot, 1) * kSlot;
+      slot = next(slot, 2);
+      uint16_t* Sn = lds + slot * kSlot;
+      issue(kOdd ? 1 : 0, S);
+      read_b(S1, 1);
+      read_a(S1, 1);
+      quad(0, 0);
+      quad(0, 1);
+      spread<2 * MF, kL, RA + RB>();
       __builtin_amdgcn_sched_barrier(0);
-      mfmas(kk & 1);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kRing - 2) * kL) : "memory");
+      asm volatile("s_barrier" ::: "memory");
+      if constexpr (kOdd) advance();
+      issue(kOdd ? 0 : 1, S1);
+      read_a(Sn, 0);
+      quad(1, 0);
+      spread<MF, kL, RA>();
+      __builtin_amdgcn_sched_barrier(0);
+      read_b(Sn, 0);
+      quad(1, 1);
+      spread<MF, 0, RB>();
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kRing - 2) * kL) : "memory");
+      asm volatile("s_barrier" ::: "memory");
+      if constexpr (!kOdd) advance();
     }
-  }
-  __syncthreads();   // waits for every load (including the zero-filling ones) and read
 
-  if constexpr (NORM) {
-    for (int64_t kt = tn; kt < kt_count; kt += tiles_n) {
-      if (kt != tn) z_chunk_load(kt);
-      z_chunk_store(kt);
-    }
-  }
-
-  // Epilogue, part 1: bias, rounding to bf16, the tile into LDS (row-major, padded).
-  // Gated form: columns [0, BN/2) hold g, [BN/2, BN) hold u of the same output columns.
-  uint16_t* E = lds;
+    // ---- epilogue (see the file comment); no LDS slot is touched, so the next tile's loads run on
+    uint32_t tm, tn;
+    tile_of(tile, a.map, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * kOut;
+    const int g = lane >> 4;
+    const int64_t col = n0 + wn * (GLU ? 32 : 64) + g * (GLU ? 8 : 16);
+    u32x4 b0 = {0u, 0u, 0u, 0u}, b1 = {0u, 0u, 0u, 0u};
+    const bool in_col = col < N;   // N is a multiple of 16: a lane's columns are wholly in or out
+    if constexpr (!GLU) {
+      if (a.bias != nullptr && !bias_staged && in_col) {
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int col = wn * TN * 32 + j * 32 + (lane & 31);
-    const float bj = (!GLU && a.bias != nullptr && n0 + col < N)
-                         ? __uint_as_float(uint32_t(a.bias[n0 + col]) << 16) : 0.0f;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wm * TM * 32 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        // norm in front: z W^T = rstd (x W^T), the row scale applied to the fp32 sum
-        const float v = NORM ? __builtin_fmaf(acc[i][j][r], rs_lds[row], bj) : acc[i][j][r] + bj;
-        E[row * C::kEpiRow + col] = uint16_t(pack_bf16x2(v, 0.0f) & 0xffffu);
+        for (int e = 0; e < 4; ++e) {
+          b0[e] = a.bias[col + 2 * e] | uint32_t(a.bias[col + 2 * e + 1]) << 16;
+          b1[e] = a.bias[col + 8 + 2 * e] | uint32_t(a.bias[col + 8 + 2 * e + 1]) << 16;
+        }
       }
-  }
-  __syncthreads();
-
-  // Part 2: thread owns output columns c16 .. c16 + 15 of rows tid / (kOut/16) + step * g.
-  constexpr int kTpr = kOut / 16;
-  static_assert(C::kThreads % kTpr == 0, "epilogue mapping");
-  const int c16 = (tid % kTpr) * 16;
-  if (n0 + c16 >= N) return;  // N is a multiple of 16: a group is wholly in or out
-  for (int row = tid / kTpr; row < BM; row += C::kThreads / kTpr) {
-    if (m0 + row >= M) break;
-    const u32x4 v0 = *reinterpret_cast<const u32x4*>(E + row * C::kEpiRow + c16);
-    const u32x4 v1 = *reinterpret_cast<const u32x4*>(E + row * C::kEpiRow + c16 + 8);
-    float f0[8], f1[8], o0[8], o1[8];
-    BF16::unpack(v0, f0);
-    BF16::unpack(v1, f1);
-    const int64_t base = (m0 + row) * N + n0 + c16;   // flat element index, multiple of 16
-    if constexpr (GLU) {
-      // Same arithmetic as the SwiGLU activation kernel on stored g and u.
-      const u32x4 u0 = *reinterpret_cast<const u32x4*>(E + row * C::kEpiRow + BN / 2 + c16);
-      const u32x4 u1 = *reinterpret_cast<const u32x4*>(E + row * C::kEpiRow + BN / 2 + c16 + 8);
-      float g0[8], g1[8];
-      BF16::unpack(u0, g0);
-      BF16::unpack(u1, g1);
+      if (bias_staged) {
+        const uint16_t* bl = bias_lds + (seq & 3) * BN + wn * 64 + g * 16;
+        b0 = *reinterpret_cast<const u32x4*>(bl);
+        b1 = *reinterpret_cast<const u32x4*>(bl + 8);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int row = wm * 2 * HM + i * 16 + (lane & 15);
+      const float rs = NORM ? rstd_lds[(seq & 3) * BM + row] : 1.0f;
+      float f0[8], f1[8], o0[8], o1[8];
+      if constexpr (GLU) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { f0[e] = 0.0f; f1[e] = 0.0f; }
+      } else {
+        BF16::unpack(b0, f0);
+        BF16::unpack(b1, f1);
+      }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        gated_value<ACT, false>(f0[e], g0[e], o0[e], g0[e]);
-        gated_value<ACT, false>(f1[e], g1[e], o1[e], g1[e]);
+        const float v0 = acc[i][e / 4][e % 4], v1 = acc[i][2 + e / 4][e % 4];
+        f0[e] = NORM ? __builtin_fmaf(v0, rs, f0[e]) : v0 + f0[e];
+        f1[e] = NORM ? __builtin_fmaf(v1, rs, f1[e]) : v1 + f1[e];
       }
-      *reinterpret_cast<u32x4*>(a.y + base) = BF16::pack(g0);
-      *reinterpret_cast<u32x4*>(a.y + base + 8) = BF16::pack(g1);
-      *reinterpret_cast<u32x4*>(a.s + base) = BF16::pack(o0);
-      *reinterpret_cast<u32x4*>(a.s + base + 8) = BF16::pack(o1);
-      *reinterpret_cast<u32x4*>(a.u + base) = u0;
-      *reinterpret_cast<u32x4*>(a.u + base + 8) = u1;
-    } else {
+      const u32x4 z0 = BF16::pack(f0), z1 = BF16::pack(f1);
+      BF16::unpack(z0, f0);
+      BF16::unpack(z1, f1);
+      const bool ok = in_col && m0 + row < M;
+      const int64_t base = (m0 + row) * N + col;
+      if constexpr (GLU) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        o0[e] = act_value<ACT, false>(f0[e]);
-        o1[e] = act_value<ACT, false>(f1[e]);
+        for (int e = 0; e < 8; ++e) gated_value<ACT, false>(f0[e], f1[e], o0[e], o1[e]);
+        const uint32_t part = codes_of<A>(f0);
+        const uint32_t other = uint32_t(__shfl_xor(int(part), 16, kWave));
+        if (ok) {
+          *reinterpret_cast<u32x4*>(a.y + base) = BF16::pack(o1);
+          *reinterpret_cast<u32x4*>(a.s + base) = BF16::pack(o0);
+          *reinterpret_cast<u32x4*>(a.u + base) = z1;
+          if ((g & 1) == 0) a.codes[base / 16] = part | (other << 16);
+          if (a.z != nullptr) *reinterpret_cast<u32x4*>(a.z + base) = z0;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          o0[e] = act_value<ACT, false>(f0[e]);
+          o1[e] = act_value<ACT, false>(f1[e]);
+        }
+        const uint32_t word = codes_of<A>(f0) | (codes_of<A>(f1) << 16);
+        if (ok) {
+          *reinterpret_cast<u32x4*>(a.y + base) = BF16::pack(o0);
+          *reinterpret_cast<u32x4*>(a.y + base + 8) = BF16::pack(o1);
+          a.codes[base / 16] = word;
+          if (a.z != nullptr) {
+            *reinterpret_cast<u32x4*>(a.z + base) = z0;
+            *reinterpret_cast<u32x4*>(a.z + base + 8) = z1;
+          }
+        }
       }
-      *reinterpret_cast<u32x4*>(a.y + base) = BF16::pack(o0);
-      *reinterpret_cast<u32x4*>(a.y + base + 8) = BF16::pack(o1);
-    }
-    a.codes[base / 16] = codes_of<A>(f0) | (codes_of<A>(f1) << 16);
-    if (a.z != nullptr) {
-      *reinterpret_cast<u32x4*>(a.z + base) = v0;
-      *reinterpret_cast<u32x4*>(a.z + base + 8) = v1;
     }
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the block
 }
 
-template <class C, int ACT, bool GLU, bool NORM = false>
-hipError_t launch_tile(const LinArgs& a, hipStream_t s) {
-  constexpr int kOut = GLU ? C::BN / 2 : C::BN;
-  const int64_t blocks = ((a.M + C::BM - 1) / C::BM) * ((a.N + kOut - 1) / kOut);
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  const size_t lds = size_t(NORM ? C::kLdsElemsNorm : C::kLdsElems) * 2;
-  // More than 64 KiB of dynamic LDS must be allowed explicitly, per kernel and device;
-  // the attribute is set on the first launch on each device.
-  constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices];
-  int dev = 0;
+constexpr int kMaxDevices = 64;
+
+// The current device and its CU count (queried once per device).
+hipError_t current_device(int& dev, int& cus) {
+  static std::atomic<int> known[kMaxDevices];
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  cus = known[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    known[dev].store(cus, std::memory_order_relaxed);
+  }
+  return hipSuccess;
+}
+
+template <class C, bool GLU>
+constexpr int kOutCols = GLU ? C::BN / 2 : C::BN;   // output columns per tile
+
+template <class C, int ACT, bool GLU, bool NORM>
+hipError_t launch_tile(LinArgs a, int dev, int cus, hipStream_t s) {
+  const int64_t tiles_m = (a.M + C::BM - 1) / C::BM;
+  const int64_t tiles_n = (a.N + kOutCols<C, GLU> - 1) / kOutCols<C, GLU>;
+  const int64_t tiles = tiles_m * tiles_n;
+  if (tiles > 0x3fffffff) return hipErrorInvalidValue;
+  a.map = {uint32_t(tiles_m), uint32_t(tiles_n), uint32_t(tiles), uint32_t(tiles / kXcds),
+           uint32_t((uint64_t(1) << 32) / uint64_t(tiles_n) - (tiles_n == 1))};
+  // More than 64 KiB of dynamic LDS must be allowed explicitly, per kernel and device;
+  // the attribute is set on the first launch on each device.
+  static std::atomic<bool> attr_set[kMaxDevices];
   if (!attr_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_act_fwd_kernel<C, ACT, GLU, NORM>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_act_fwd_kernel<C, ACT, GLU, NORM>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
     if (e != hipSuccess) return e;
     attr_set[dev].store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((linear_act_fwd_kernel<C, ACT, GLU, NORM>), dim3(unsigned(blocks)),
-                     dim3(C::kThreads), lds, s, a);
+  const int64_t slots = int64_t(cus) * C::kBlocksPerCu;
+  hipLaunchKernelGGL((linear_act_fwd_kernel<C, ACT, GLU, NORM>), dim3(unsigned(tiles < slots ? tiles : slots)),
+                     dim3(C::kThreads), C::kLdsBytes, s, a);
   return hipGetLastError();
 }
 
-#ifndef LMBP_LIN_BIG_MIN_ROUNDS
-// Use the 256 x 256 tiles when they fill at least this many rounds of the GPU's CUs
-// (one block per CU); otherwise the 128 x 128 tiles (two blocks per CU) waste less of the
-// last round. Measured: the ViT-B MLP projection (2.3 rounds) runs faster with the small
-// tiles, the LLaMA-7B gate projection (5.4 rounds) with the large ones.
-#define LMBP_LIN_BIG_MIN_ROUNDS 4
-#endif
+// Estimated time of a tile configuration, in us: full rounds of the resident blocks and a
+// partial one, in which a CU with fewer blocks is faster. The coefficients are a
+// least-squares fit (relative error 7 to 10% rms) to the measured times of each
+// configuration on M = 16 .. 12608 rows of seven layers (K x N = 512 x 2048, 768 x 3072,
+// 1000 x 4000, 1024 x 4096 with GELU; 2048 x 5632, 4096 x 11008, 5120 x 13824 gated), 256
+// CUs. Taking the configuration that the model prefers was within 0.6% of the fastest one
+// on average (at worst 13%). The single rule used before (256 x 256 tiles from four rounds
+// of them on, else 128 x 128) was 18% slower on average: 1024 rows of the 4096 x 11008
+// gated layer 213 us against 181, 2048 rows 416 against 302.
+struct Cost {
+  float base, step_full, step_any, step_second, step_third, step_load, full, any, second;
+};
+template <class C, bool GLU>
+float cost(const LinArgs& a, int cus, const Cost& c) {
+  const int64_t tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + kOutCols<C, GLU> - 1) / kOutCols<C, GLU>);
+  const int64_t slots = int64_t(cus) * C::kBlocksPerCu;
+  const int64_t full = tiles / slots, rest = tiles % slots;
+  const float any = rest > 0, second = rest > cus, third = rest > 2 * int64_t(cus);
+  const float per_step = c.step_full * float(full) + c.step_any * any + c.step_second * second +
+                         c.step_third * third + c.step_load * (float(rest) / float(slots));
+  return c.base + float((a.K + kBK - 1) / kBK) * per_step + c.full * float(full) + c.any * any + c.second * second;
+}
+constexpr Cost kBigCost = {5.53f, 1.386f, 0.844f, 0.0f, 0.0f, 0.735f, 17.28f, 10.29f, 0.0f};
+constexpr Cost kMidCost = {10.13f, 1.567f, 0.739f, 0.241f, 0.0f, 0.901f, 14.30f, 0.33f, 5.46f};
+constexpr Cost kSmallCost = {4.51f, 1.027f, 0.468f, 0.257f, 0.0f, 0.569f, 6.06f, 0.21f, 0.96f};
+constexpr Cost kLowCost = {2.87f, 1.091f, 0.484f, 0.177f, 0.164f, 0.447f, 2.32f, 0.0f, 0.0f};
+
+template <int ACT, bool GLU, bool NORM>
+hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
+  int dev = 0, cus = 0;
+  const hipError_t e = current_device(dev, cus);
+  if (e != hipSuccess) return e;
+  const float big = cost<BigTile, GLU>(a, cus, kBigCost), mid = cost<MidTile, GLU>(a, cus, kMidCost);
+  const float small = cost<SmallTile, GLU>(a, cus, kSmallCost), low = cost<LowTile, GLU>(a, cus, kLowCost);
+  if (big <= mid && big <= small && big <= low) return launch_tile<BigTile, ACT, GLU, NORM>(a, dev, cus, s);
+  if (mid <= small && mid <= low) return launch_tile<MidTile, ACT, GLU, NORM>(a, dev, cus, s);
+  if (small <= low) return launch_tile<SmallTile, ACT, GLU, NORM>(a, dev, cus, s);
+  return launch_tile<LowTile, ACT, GLU, NORM>(a, dev, cus, s);
+}
 
 }  // namespace lin
-
-namespace {
-// Large tiles when they fill at least LMBP_LIN_BIG_MIN_ROUNDS rounds of the CUs.
-bool use_big_tiles(int64_t M, int64_t N_tile_cols) {
-  int device = 0, cus = 256;
-  if (hipGetDevice(&device) == hipSuccess)
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
-  const int64_t big_tiles = ((M + lin::BigTile::BM - 1) / lin::BigTile::BM) *
-                            ((N_tile_cols + lin::BigTile::BN - 1) / lin::BigTile::BN);
-  return big_tiles >= int64_t(LMBP_LIN_BIG_MIN_ROUNDS) * cus;
-}
-}  // namespace
 
 hipError_t launch_linear_act_fwd(int act, int64_t M, int64_t N, int64_t K, const void* x,
                                  const void* w, const void* bias, void* y, uint32_t* codes,
                                  void* z, hipStream_t s) {
-  lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), nullptr,
-                 static_cast<const uint16_t*>(bias), static_cast<uint16_t*>(y), nullptr,
-                 nullptr, codes, static_cast<uint16_t*>(z), M, N, K, nullptr, nullptr};
-  const bool big = use_big_tiles(M, N);
-  using lin::BigTile;
-  using lin::SmallTile;
-  using lin::launch_tile;
-  if (act == kGelu)
-    return big ? launch_tile<BigTile, kGelu, false>(a, s) : launch_tile<SmallTile, kGelu, false>(a, s);
-  return big ? launch_tile<BigTile, kSilu, false>(a, s) : launch_tile<SmallTile, kSilu, false>(a, s);
+  const lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), nullptr,
+                       static_cast<const uint16_t*>(bias), static_cast<uint16_t*>(y), nullptr,
+                       nullptr, codes, static_cast<uint16_t*>(z), M, N, K, nullptr, {}};
+  return act == kGelu ? lin::launch_lin<kGelu, false, false>(a, s) : lin::launch_lin<kSilu, false, false>(a, s);
 }
 
 hipError_t launch_linear_glu_fwd(int64_t M, int64_t N, int64_t K, const void* x, const void* w_gate,
                                  const void* w_up, void* h, void* s_out, void* u, uint32_t* codes,
                                  void* g, hipStream_t s) {
-  lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_gate),
-                 static_cast<const uint16_t*>(w_up), nullptr, static_cast<uint16_t*>(h),
-                 static_cast<uint16_t*>(s_out), static_cast<uint16_t*>(u), codes,
-                 static_cast<uint16_t*>(g), M, N, K, nullptr, nullptr};
-  // Each block covers half as many output columns as its tile width.
-  const bool big = use_big_tiles(M, 2 * N);
-  return big ? lin::launch_tile<lin::BigTile, kSilu, true>(a, s)
-             : lin::launch_tile<lin::SmallTile, kSilu, true>(a, s);
+  const lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_gate),
+                       static_cast<const uint16_t*>(w_up), nullptr, static_cast<uint16_t*>(h),
+                       static_cast<uint16_t*>(s_out), static_cast<uint16_t*>(u), codes,
+                       static_cast<uint16_t*>(g), M, N, K, nullptr, {}};
+  return lin::launch_lin<kSilu, true, false>(a, s);
 }
 
 hipError_t launch_linear_rms_act_fwd(int act, int64_t M, int64_t N, int64_t K, float eps,
                                      const void* x, const void* w, const void* bias, void* y,
                                      uint32_t* codes, void* pre, void* z_norm, float* rstd,
                                      hipStream_t s) {
-  hipError_t e = launch_norm_fwd(false, true, M, K, eps, x, nullptr, rstd, true, s);
+  hipError_t e = launch_norm_fwd(false, true, M, K, eps, x, z_norm, rstd, true, s);
   if (e != hipSuccess) return e;
-  lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), nullptr,
-                 static_cast<const uint16_t*>(bias), static_cast<uint16_t*>(y), nullptr,
-                 nullptr, codes, static_cast<uint16_t*>(pre), M, N, K, rstd,
-                 static_cast<uint16_t*>(z_norm)};
-  const bool big = use_big_tiles(M, N);
-  using lin::BigTile;
-  using lin::SmallTile;
-  using lin::launch_tile;
-  if (act == kGelu)
-    return big ? launch_tile<BigTile, kGelu, false, true>(a, s) : launch_tile<SmallTile, kGelu, false, true>(a, s);
-  return big ? launch_tile<BigTile, kSilu, false, true>(a, s) : launch_tile<SmallTile, kSilu, false, true>(a, s);
+  const lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), nullptr,
+                       static_cast<const uint16_t*>(bias), static_cast<uint16_t*>(y), nullptr,
+                       nullptr, codes, static_cast<uint16_t*>(pre), M, N, K, rstd, {}};
+  return act == kGelu ? lin::launch_lin<kGelu, false, true>(a, s) : lin::launch_lin<kSilu, false, true>(a, s);
 }
 
 hipError_t launch_linear_rms_glu_fwd(int64_t M, int64_t N, int64_t K, float eps, const void* x,
                                      const void* w_gate, const void* w_up, void* h, void* s_out,
                                      void* u, uint32_t* codes, void* g, void* z_norm, float* rstd,
                                      hipStream_t s) {
-  hipError_t e = launch_norm_fwd(false, true, M, K, eps, x, nullptr, rstd, true, s);
+  hipError_t e = launch_norm_fwd(false, true, M, K, eps, x, z_norm, rstd, true, s);
   if (e != hipSuccess) return e;
-  lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_gate),
-                 static_cast<const uint16_t*>(w_up), nullptr, static_cast<uint16_t*>(h),
-                 static_cast<uint16_t*>(s_out), static_cast<uint16_t*>(u), codes,
-                 static_cast<uint16_t*>(g), M, N, K, rstd, static_cast<uint16_t*>(z_norm)};
-  const bool big = use_big_tiles(M, 2 * N);
-  return big ? lin::launch_tile<lin::BigTile, kSilu, true, true>(a, s)
-             : lin::launch_tile<lin::SmallTile, kSilu, true, true>(a, s);
+  const lin::LinArgs a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_gate),
+                       static_cast<const uint16_t*>(w_up), nullptr, static_cast<uint16_t*>(h),
+                       static_cast<uint16_t*>(s_out), static_cast<uint16_t*>(u), codes,
+                       static_cast<uint16_t*>(g), M, N, K, rstd, {}};
+  return lin::launch_lin<kSilu, true, true>(a, s);
 }
 
 }  // namespace lmbp

@@ -1,0 +1,90 @@
+"""Fused linear layers in every tile configuration, at the sizes where one can go wrong:
+ragged last tiles, one K step (the load stream runs two tiles ahead), one row or column
+more or less than a whole tile, more tiles than resident blocks, and a bias between words.
+
+Inputs are small integers times powers of two, so every product and every fp32 sum is
+exact in any order (|sum| < 2^24 units): the stored pre-activation must equal the rounding
+of torch's fp32 product bit for bit, and y and the codes must be what the activation
+kernels make of it."""
+
+import pytest
+
+torch = pytest.importorskip("torch")
+import paper_2406_16282_amd as lmbp  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dyadic(shape, exp, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return torch.randint(-8, 9, shape, generator=g, device=DEV).float() * 2.0 ** exp
+
+
+def product(x, w, b=None):
+    z = x @ w.t()   # fp32, exact
+    return (z if b is None else z + b).bfloat16()
+
+
+# rows x output features x input features; the comments name the tile (rows x columns).
+SHAPES = [
+    (1, 16, 8), (63, 144, 64), (65, 112, 72), (777, 3088, 136), (8000, 8208, 8),   # 64 x 128
+    (1999, 3088, 72), (3001, 2064, 72), (9001, 2064, 640),                         # 128 x 128
+    (3001, 8176, 520), (4097, 5648, 776),                                          # 128 x 256
+    (1999, 6160, 520), (3001, 4112, 520), (4097, 3056, 520), (4100, 11008, 1032),  # 256 x 256
+]
+
+
+@pytest.mark.parametrize("act", ["gelu", "silu"])
+@pytest.mark.parametrize("m,n,k", SHAPES)
+def test_plain(m, n, k, act):
+    print(f"[tiles] plain {m} {n} {k} {act}", flush=True)
+    x, w, b = dyadic((m, k), -3, 1), dyadic((n, k), -4, 2), dyadic((n,), -7, 3)
+    y, codes, z = lmbp.linear_act_fwd(x.bfloat16(), w.bfloat16(), b.bfloat16(), act=act, store_z=True)
+    ref = product(x, w, b)
+    assert torch.equal(z, ref)
+    y_r, c_r = (lmbp.regelu2_fwd if act == "gelu" else lmbp.resilu2_fwd)(ref)
+    assert torch.equal(y.view(torch.int16), y_r.view(torch.int16))
+    assert torch.equal(codes, c_r)
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 16, 8), (63, 80, 64), (700, 1552, 8), (4097, 4112, 8), (3001, 1040, 72),
+                                   (1025, 3056, 72), (4097, 5648, 520), (1999, 5648, 776), (1999, 3088, 520),
+                                   (2049, 3056, 520), (2048, 11008, 1032)])
+def test_gated(m, n, k):
+    print(f"[tiles] gated {m} {n} {k}", flush=True)
+    x, wg, wu = dyadic((m, k), -3, 1), dyadic((n, k), -4, 2), dyadic((n, k), -4, 3)
+    h, s, u, codes, g = lmbp.linear_swiglu_fwd(x.bfloat16(), wg.bfloat16(), wu.bfloat16(), store_g=True)
+    g_r, u_r = product(x, wg), product(x, wu)
+    assert torch.equal(g, g_r) and torch.equal(u, u_r)
+    h_r, s_r, c_r = lmbp.reswiglu2_fwd(g_r, u_r)
+    for a, r in ((h, h_r), (s, s_r)):
+        assert torch.equal(a.view(torch.int16), r.view(torch.int16))
+    assert torch.equal(codes, c_r)
+
+
+@pytest.mark.parametrize("m,n,k", [(130, 144, 72), (1999, 3088, 72), (3001, 8176, 520), (3001, 4112, 520)])
+def test_bias_between_words(m, n, k):
+    """A bias that starts 2 bytes past a 4-byte word gives the same bytes as an aligned one."""
+    x, w, b = dyadic((m, k), -3, 1).bfloat16(), dyadic((n, k), -4, 2).bfloat16(), dyadic((n,), -7, 3).bfloat16()
+    room = torch.zeros(n + 3, dtype=torch.bfloat16, device=DEV)
+    odd = room[1:n + 1]
+    assert odd.data_ptr() % 4 == 2
+    odd.copy_(b)
+    for a, r in zip(lmbp.linear_act_fwd(x, w, odd, store_z=True), lmbp.linear_act_fwd(x, w, b, store_z=True)):
+        assert torch.equal(a, r)
+
+
+@pytest.mark.parametrize("m,n,k", [(65, 112, 72), (1999, 3088, 72), (3001, 8176, 520), (3001, 4112, 520)])
+def test_norm_in_front(m, n, k):
+    """z and rstd are the norm kernel's; x w^T is exact in fp32, so the pre-activation is
+    within one fp32 and one bf16 rounding (2^-24 and 2^-8 of the value) of rstd (x w^T)."""
+    x, w = dyadic((m, k), -3, 1), dyadic((n, k), -4, 2)
+    y, codes, z, rstd, pre = lmbp.msrms_linear_act_fwd(x.bfloat16(), w.bfloat16(), 1e-5, store_pre=True)
+    z_r, rstd_r = lmbp.msrms_fwd(x.bfloat16(), 1e-5)
+    assert torch.equal(z, z_r) and torch.equal(rstd, rstd_r.reshape(-1))
+    exact = (x @ w.t()).double() * rstd.double()[:, None]
+    assert ((pre.double() - exact).abs() <= exact.abs() * 2.0 ** -8 * (1 + 1e-4)).all()
+    y_r, c_r = lmbp.resilu2_fwd(pre)
+    assert torch.equal(y.view(torch.int16), y_r.view(torch.int16)) and torch.equal(codes, c_r)
