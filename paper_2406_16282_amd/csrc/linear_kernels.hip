@@ -23,8 +23,9 @@
 // beside the other's MFMAs (78 us, against 83-86 us for either of the other tiles).
 //
 // Tiling. A block computes a BM x BN tile of z with WM x WN waves, each BM/WM x 64 as
-// 16 x 16 MFMA tiles, accumulators in registers. Four tiles are compiled; the launcher
-// picks one by a cost model of the measured times (below).
+// 16 x 16 MFMA tiles, accumulators in registers. Four tiles are compiled, and a
+// split-K form for few rows; the launcher picks one by a cost model of the measured times
+// (below).
 //
 // K loop. K advances in steps of 64, each in two half steps. The LDS is a ring of slots
 // of half a step's operands: slot 2t holds the first half of every wave's rows of x and
@@ -68,6 +69,7 @@
 #include "act_math.hpp"
 #include "lmbp_launch.hpp"
 
+#include <algorithm>
 #include <atomic>
 
 namespace lmbp {
@@ -121,8 +123,10 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t byt
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kBufferGDword3);
 }
 // 16 or 4 bytes per lane from the buffer into LDS at `dst` + lane * 16 or 4 (dst wave-uniform).
+// CPOL: cache policy bits of the instruction (nt = 2).
+template <int CPOL = 0>
 __device__ inline void load_lds16(__amdgpu_buffer_rsrc_t r, void* dst, uint32_t offset) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, offset, 0, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, offset, 0, 0, CPOL);
 }
 __device__ inline void load_lds4(__amdgpu_buffer_rsrc_t r, void* dst, uint32_t offset) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 4, offset, 0, 0, 0);
@@ -455,6 +459,170 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void linear_act_fwd_kern
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the block
 }
 
+// Few rows: the split-K form. What bounds it: for large weights the stream of W, each row
+// of which serves at most 32 rows of x, so what counts is how many bytes are in flight
+// over the whole device and that every lane quad asks for consecutive bytes; for small
+// weights the latency of one chain of loads. A block of 4 waves takes MT x 16 rows of x
+// and 32 rows of W (gated: 16 of each weight). Its waves take the K steps of 64 in turn,
+// each through an LDS ring of its own with two steps in flight, so that the K loop has no
+// barrier. The four partial sums of a result meet in LDS, are added in a fixed order, and
+// go through the epilogue with 4 columns per lane, four lanes to a code word.
+// Measured against the tiled kernel's best form: [16 x 768] x 3072 3.9 against 8.6 us;
+// [16 x 4096] x two 11008 33 against 43-46 us (180 MB of weights, 5.5 TB/s). MFMA operands
+// loaded straight into registers asked for 16 bytes per row and lane: 46 us; eight waves
+// to a block 37.7, three steps in flight 35.8, two waves to a block 38 us, against 35.1
+// (all before NT).
+// NT: W by non-temporal loads, when it is read once and does not fit the caches
+// (180 MB: 33 against 37 us; 4.7 MB, resident, 4.2 against 3.9 us).
+constexpr int kRowsWaves = 4, kRowsDepth = 2;
+template <int MT>
+constexpr int kRowsLds = kRowsWaves * kRowsDepth * (32 + MT * 16) * kBK * 2;
+
+template <int MT, bool NT, int ACT, bool GLU, bool NORM>
+__global__ __launch_bounds__(kRowsWaves * kWave) void linear_act_fwd_rows_kernel(LinArgs a) {
+  using A = ActOf<ACT>;
+  constexpr int kWaves = kRowsWaves, D = kRowsDepth, kRows = MT * 16, kOut = GLU ? 16 : 32;
+  static_assert(2 * MT <= kWaves && kRowsLds<MT> <= 64 * 1024, "one result tile per wave; LDS");
+  const int64_t M = a.M, N = a.N, K = a.K;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = wave_in_block();
+  // Row blocks of one column block run on one XCD, next to each other.
+  const uint32_t b = blockIdx.x;
+  const uint32_t id = (b < a.map.per_xcd * kXcds) ? (b % kXcds) * a.map.per_xcd + b / kXcds : b;
+  const int64_t m0 = int64_t(id % a.map.tiles_m) * kRows, n0 = int64_t(id / a.map.tiles_m) * kOut;
+  const int64_t rows_x = (M - m0 < kRows) ? M - m0 : kRows;
+  const int64_t rows_w = (N - n0 < kOut) ? N - n0 : kOut;
+  const auto rx = make_rsrc(a.x + m0 * K, rows_x * K * 2);
+  const auto rw = make_rsrc(a.w + n0 * K, rows_w * K * 2);
+  const auto rw2 = make_rsrc((GLU ? a.w2 : a.w) + n0 * K, rows_w * K * 2);
+  const int g = lane >> 4;
+  // This wave's ring: D steps of 32 rows of W and kRows of x, 128 bytes a row, swizzled as
+  // the x rows of the tiled kernel. No other wave touches it: no barrier in the K loop.
+  constexpr int kStep = (32 + kRows) * kBK, kLoads = 4 + 2 * MT;
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  uint16_t* const ring = lds + wave * D * kStep;
+  const int r_in = lane / 8, kc = ((lane % 8) ^ (r_in >> 1)) * 8;   // rows 8 q + r_in: q even
+  const int kc_odd = ((lane % 8) ^ (4 + (r_in >> 1))) * 8;          // q odd
+  const uint32_t off_even = uint32_t(r_in * K * 2 + kc * 2), off_odd = uint32_t((8 + r_in) * K * 2 + kc_odd * 2);
+  const uint32_t tile_off = uint32_t(16 * K * 2);
+  auto load = [&](int step, int d) {
+    uint16_t* S = ring + d * kStep;
+    const uint32_t k0 = uint32_t(step) * kBK;
+    const uint32_t even = k0 + kc < K ? off_even + k0 * 2 : kOutOfRange;
+    const uint32_t odd = k0 + kc_odd < K ? off_odd + k0 * 2 : kOutOfRange;
+    load_lds16<NT ? 2 : 0>(rw, S, even);
+    load_lds16<NT ? 2 : 0>(rw, S + 512, odd);
+    load_lds16<NT ? 2 : 0>(GLU ? rw2 : rw, S + 1024, (GLU || even == kOutOfRange) ? even : even + tile_off);
+    load_lds16<NT ? 2 : 0>(GLU ? rw2 : rw, S + 1536, (GLU || odd == kOutOfRange) ? odd : odd + tile_off);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      load_lds16(rx, S + 2048 + i * 1024, even == kOutOfRange ? even : even + uint32_t(i) * tile_off);
+      load_lds16(rx, S + 2048 + i * 1024 + 512, odd == kOutOfRange ? odd : odd + uint32_t(i) * tile_off);
+    }
+  };
+  f32x4 acc[MT][2];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int steps = int((K + kBK - 1) / kBK);
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(wave + d * kWaves, d);   // steps past the end read zeros
+  const int frag = (lane & 15) * kBK, sw = (lane & 15) >> 1;
+  const int u0 = (g ^ sw) * 8, u1 = ((4 + g) ^ sw) * 8;
+  int d = 0;
+  for (int st = wave; st < steps; st += kWaves) {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((D - 1) * kLoads) : "memory");
+    const uint16_t* S = ring + d * kStep + frag;
+    bf16x8 fw[2][2], fx[MT][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      fw[j][0] = *reinterpret_cast<const bf16x8*>(S + j * 1024 + u0);
+      fw[j][1] = *reinterpret_cast<const bf16x8*>(S + j * 1024 + u1);
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      fx[i][0] = *reinterpret_cast<const bf16x8*>(S + 2048 + i * 1024 + u0);
+      fx[i][1] = *reinterpret_cast<const bf16x8*>(S + 2048 + i * 1024 + u1);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before it is loaded over
+    load(st + D * kWaves, d);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][kk], fx[i][kk], acc[i][j], 0, 0, 0);
+    d = d + 1 == D ? 0 : d + 1;
+  }
+  __syncthreads();   // every load has landed and every ring is read: its place holds the sums
+  auto part = reinterpret_cast<f32x4 (*)[MT][2][kWave]>(lds);
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) part[wave][i][j][lane] = acc[i][j];
+  __syncthreads();
+
+  auto total = [&](int i, int j) {
+    f32x4 t = part[0][i][j][lane];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      const f32x4 p = part[w][i][j][lane];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t[r] += p[r];
+    }
+    return t;
+  };
+  // Gated: wave i takes row tile i; plain: wave 2 i + j takes row tile i, column tile j.
+  constexpr int kParts = GLU ? MT : 2 * MT;
+  if (wave >= kParts) return;
+  const int i = GLU ? wave : wave / 2, j = GLU ? 0 : wave % 2;
+  const int64_t row = m0 + i * 16 + (lane & 15), col = n0 + j * 16 + g * 4;
+  const bool ok = row < M && col < N;
+  const int64_t base = row * N + col;
+  const float rs = (NORM && row < M) ? a.rstd[row] : 1.0f;
+  f32x4 v = total(i, j);
+  float f[4], o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float bj = (!GLU && a.bias != nullptr && ok) ? __uint_as_float(uint32_t(a.bias[col + e]) << 16) : 0.0f;
+    f[e] = NORM ? __builtin_fmaf(v[e], rs, bj) : v[e] + bj;
+  }
+  const uint2 z = {pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
+  auto unpack = [](const uint2& q, float (&t)[4]) {
+    t[0] = __uint_as_float(q.x << 16);
+    t[1] = __uint_as_float(q.x & 0xffff0000u);
+    t[2] = __uint_as_float(q.y << 16);
+    t[3] = __uint_as_float(q.y & 0xffff0000u);
+  };
+  unpack(z, f);
+  uint32_t word = codes_of<A>(f) << (8 * g);
+  word |= uint32_t(__shfl_xor(int(word), 16, kWave));
+  word |= uint32_t(__shfl_xor(int(word), 32, kWave));
+  if constexpr (GLU) {
+    const f32x4 vu = total(i, 1);
+    float fu[4], h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) fu[e] = NORM ? vu[e] * rs : vu[e];
+    const uint2 u = {pack_bf16x2(fu[0], fu[1]), pack_bf16x2(fu[2], fu[3])};
+    unpack(u, fu);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gated_value<ACT, false>(f[e], fu[e], o[e], h[e]);
+    if (!ok) return;
+    *reinterpret_cast<uint2*>(a.y + base) = uint2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
+    *reinterpret_cast<uint2*>(a.s + base) = uint2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+    *reinterpret_cast<uint2*>(a.u + base) = u;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = act_value<ACT, false>(f[e]);
+    if (!ok) return;
+    *reinterpret_cast<uint2*>(a.y + base) = uint2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+  }
+  if (g == 0) a.codes[base / 16] = word;
+  if (a.z != nullptr) *reinterpret_cast<uint2*>(a.z + base) = z;
+}
+
 constexpr int kMaxDevices = 64;
 
 // The current device and its CU count (queried once per device).
@@ -525,6 +693,37 @@ constexpr Cost kMidCost = {10.13f, 1.567f, 0.739f, 0.241f, 0.0f, 0.901f, 14.30f,
 constexpr Cost kSmallCost = {4.51f, 1.027f, 0.468f, 0.257f, 0.0f, 0.569f, 6.06f, 0.21f, 0.96f};
 constexpr Cost kLowCost = {2.87f, 1.091f, 0.484f, 0.177f, 0.164f, 0.447f, 2.32f, 0.0f, 0.0f};
 
+// The same for the split-K form, fitted to 16 .. 512 rows of the same layers: a latency,
+// the chain of a wave's K steps, and the bytes that all blocks take in (per MB, 256 CUs).
+// With it 0.7% over the fastest form on average.
+struct RowsCost {
+  float base, step, mb;
+};
+constexpr RowsCost kRows16Cost = {1.59f, 0.542f, 0.0578f}, kRows32Cost = {2.21f, 0.401f, 0.0625f};
+template <int MT, bool GLU>
+float rows_cost(const LinArgs& a, int cus, const RowsCost& c) {
+  constexpr int kOut = GLU ? 16 : 32;
+  const float blocks = float((a.M + MT * 16 - 1) / (MT * 16)) * float((a.N + kOut - 1) / kOut);
+  const float steps = float((a.K + kBK - 1) / kBK);
+  return c.base + c.step * steps / kRowsWaves +
+         c.mb * blocks * steps * float((32 + MT * 16) * kBK * 2) * 1e-6f * 256.0f / float(cus);
+}
+
+template <int MT, int ACT, bool GLU, bool NORM>
+hipError_t launch_rows(LinArgs a, hipStream_t s) {
+  constexpr int kOut = GLU ? 16 : 32;
+  const int64_t tiles_m = (a.M + MT * 16 - 1) / (MT * 16), tiles_n = (a.N + kOut - 1) / kOut;
+  const int64_t blocks = tiles_m * tiles_n;
+  if (blocks > 0x3fffffff) return hipErrorInvalidValue;
+  a.map = {uint32_t(tiles_m), uint32_t(tiles_n), uint32_t(blocks), uint32_t(blocks / kXcds), 0u};
+  // Non-temporal from 32 MiB of weights on, when one row block reads them (see the kernel).
+  const bool nt = tiles_m == 1 && a.N * a.K * (GLU ? 4 : 2) > (int64_t(32) << 20);
+  const auto kernel = nt ? linear_act_fwd_rows_kernel<MT, true, ACT, GLU, NORM>
+                         : linear_act_fwd_rows_kernel<MT, false, ACT, GLU, NORM>;
+  hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(kRowsWaves * kWave), kRowsLds<MT>, s, a);
+  return hipGetLastError();
+}
+
 template <int ACT, bool GLU, bool NORM>
 hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
   int dev = 0, cus = 0;
@@ -532,6 +731,10 @@ hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   const float big = cost<BigTile, GLU>(a, cus, kBigCost), mid = cost<MidTile, GLU>(a, cus, kMidCost);
   const float small = cost<SmallTile, GLU>(a, cus, kSmallCost), low = cost<LowTile, GLU>(a, cus, kLowCost);
+  const float rows16 = rows_cost<1, GLU>(a, cus, kRows16Cost), rows32 = rows_cost<2, GLU>(a, cus, kRows32Cost);
+  const float tiled = std::min(std::min(big, mid), std::min(small, low));
+  if (rows16 < tiled && rows16 <= rows32) return launch_rows<1, ACT, GLU, NORM>(a, s);
+  if (rows32 < tiled) return launch_rows<2, ACT, GLU, NORM>(a, s);
   if (big <= mid && big <= small && big <= low) return launch_tile<BigTile, ACT, GLU, NORM>(a, dev, cus, s);
   if (mid <= small && mid <= low) return launch_tile<MidTile, ACT, GLU, NORM>(a, dev, cus, s);
   if (small <= low) return launch_tile<SmallTile, ACT, GLU, NORM>(a, dev, cus, s);

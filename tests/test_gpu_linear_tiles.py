@@ -29,7 +29,9 @@ def product(x, w, b=None):
 
 # rows x output features x input features; the comments name the tile (rows x columns).
 SHAPES = [
-    (1, 16, 8), (63, 144, 64), (65, 112, 72), (777, 3088, 136), (8000, 8208, 8),   # 64 x 128
+    (1, 16, 8), (16, 3072, 768), (17, 48, 264), (31, 16, 1032), (33, 1040, 776),   # split K
+    (90, 528, 520), (200, 2064, 136), (5, 16400, 2056),
+    (777, 3088, 136), (3000, 4112, 72), (8000, 8208, 8),                           # 64 x 128
     (1999, 3088, 72), (3001, 2064, 72), (9001, 2064, 640),                         # 128 x 128
     (3001, 8176, 520), (4097, 5648, 776),                                          # 128 x 256
     (1999, 6160, 520), (3001, 4112, 520), (4097, 3056, 520), (4100, 11008, 1032),  # 256 x 256
@@ -49,7 +51,8 @@ def test_plain(m, n, k, act):
     assert torch.equal(codes, c_r)
 
 
-@pytest.mark.parametrize("m,n,k", [(1, 16, 8), (63, 80, 64), (700, 1552, 8), (4097, 4112, 8), (3001, 1040, 72),
+@pytest.mark.parametrize("m,n,k", [(1, 16, 8), (16, 11008, 520), (17, 48, 264), (29, 5632, 2056), (100, 80, 776),
+                                   (2, 16400, 1032), (700, 1552, 8), (4097, 4112, 8), (3001, 1040, 72),
                                    (1025, 3056, 72), (4097, 5648, 520), (1999, 5648, 776), (1999, 3088, 520),
                                    (2049, 3056, 520), (2048, 11008, 1032)])
 def test_gated(m, n, k):
@@ -64,7 +67,7 @@ def test_gated(m, n, k):
     assert torch.equal(codes, c_r)
 
 
-@pytest.mark.parametrize("m,n,k", [(130, 144, 72), (1999, 3088, 72), (3001, 8176, 520), (3001, 4112, 520)])
+@pytest.mark.parametrize("m,n,k", [(13, 144, 72), (1000, 3088, 72), (1999, 3088, 72), (3001, 8176, 520), (3001, 4112, 520)])
 def test_bias_between_words(m, n, k):
     """A bias that starts 2 bytes past a 4-byte word gives the same bytes as an aligned one."""
     x, w, b = dyadic((m, k), -3, 1).bfloat16(), dyadic((n, k), -4, 2).bfloat16(), dyadic((n,), -7, 3).bfloat16()
@@ -76,7 +79,7 @@ def test_bias_between_words(m, n, k):
         assert torch.equal(a, r)
 
 
-@pytest.mark.parametrize("m,n,k", [(65, 112, 72), (1999, 3088, 72), (3001, 8176, 520), (3001, 4112, 520)])
+@pytest.mark.parametrize("m,n,k", [(1, 16, 8), (65, 112, 72), (27, 2064, 2056), (900, 3088, 72), (1999, 3088, 72), (3001, 8176, 520), (3001, 4112, 520)])
 def test_norm_in_front(m, n, k):
     """z and rstd are the norm kernel's; x w^T is exact in fp32, so the pre-activation is
     within one fp32 and one bf16 rounding (2^-24 and 2^-8 of the value) of rstd (x w^T)."""
