@@ -267,6 +267,31 @@ lmbp_status msrms_linear_swiglu_fwd(lmbp_dtype dt, int64_t m, int64_t n, int64_t
                                     float *rstd, void *stream);
 
 /* ------------------------------------------------------------------------
+ * Backward of the fused linear layers with respect to their parameters.
+ *
+ *   linear_weight_grad : dw = bf16( dz^T x ), sums over the m rows in fp32, one rounding.
+ *   linear_act_bwd     : dz = dy * slope[code] (as regelu2_bwd / resilu2_bwd; db of the
+ *                        column sums of the rounded dz, fp32 sums, one rounding) and dw.
+ *
+ *   dt  : LMBP_BF16 only. m, n, k >= 0; n a multiple of 16, k of 8; n, k <= 2^24.
+ *   dz, dy [m x n], x [m x k], dw [n x k], db [n]. linear_act_bwd: codes as written by
+ *         the forward; dw NULL: not computed (x is then not used); dx == dy of an
+ *         activation backward is not allowed here: dz overlaps no other buffer.
+ *   workspace : lmbp_linear_grad_bytes(m, n, k, bias) bytes on the calling thread's
+ *         current device, 16-byte aligned (bias: nonzero for linear_act_bwd). NULL if
+ *         that is 0. Its contents do not matter before or after.
+ * All tensors 16-byte aligned (db: 2, codes: 4); m == 0 gives zeros.
+ * ------------------------------------------------------------------------ */
+size_t lmbp_linear_grad_bytes(int64_t m, int64_t n, int64_t k, int bias);
+lmbp_status linear_weight_grad(lmbp_dtype dt, int64_t m, int64_t n, int64_t k, const void *dz,
+                               const void *x, void *dw, void *workspace, int64_t workspace_bytes,
+                               void *stream);
+lmbp_status linear_act_bwd(lmbp_act act, lmbp_dtype dt, int64_t m, int64_t n, int64_t k,
+                           const void *dy, const uint32_t *codes, const void *x, void *dz,
+                           void *dw, void *db, void *workspace, int64_t workspace_bytes,
+                           void *stream);
+
+/* ------------------------------------------------------------------------
  * Measurement utility (not part of the method): copies `bytes` bytes from src
  * to dst with 16-byte non-temporal vector loads and non-temporal device-scope vector
  * stores (written through the L2), the fastest plain copy measured on the GPU for

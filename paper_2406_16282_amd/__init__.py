@@ -19,8 +19,10 @@ from .binding import (  # noqa: F401
     codes_words,
     copy_bytes,
     lib,
+    linear_act_bwd,
     linear_act_fwd,
     linear_swiglu_fwd,
+    linear_weight_grad,
     msln_bwd,
     msln_fwd,
     msrms_bwd,

@@ -85,6 +85,12 @@ def lib():
     L.msrms_linear_act_fwd.restype = i32
     L.msrms_linear_swiglu_fwd.argtypes = [i32, i64, i64, i64, f32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.msrms_linear_swiglu_fwd.restype = i32
+    L.lmbp_linear_grad_bytes.argtypes = [i64, i64, i64, i32]
+    L.lmbp_linear_grad_bytes.restype = ctypes.c_size_t
+    L.linear_weight_grad.argtypes = [i32, i64, i64, i64, vp, vp, vp, vp, i64, vp]
+    L.linear_weight_grad.restype = i32
+    L.linear_act_bwd.argtypes = [i32, i32, i64, i64, i64, vp, vp, vp, vp, vp, vp, vp, i64, vp]
+    L.linear_act_bwd.restype = i32
     L.lmbp_copy.argtypes = [vp, vp, i64, vp]
     L.lmbp_copy.restype = i32
     _lib = L
@@ -430,6 +436,58 @@ def linear_act_fwd(x, w, bias=None, act="gelu", y=None, codes=None, z=None, stor
                                                   _ptr(y), _ptr(codes),
                                                   _ptr(z) if z is not None else None, _stream(x, stream)))
     return (y, codes, z) if z is not None else (y, codes)
+
+
+def _bf16_matrix(t, ref, what):
+    _on(t, ref, what)
+    if t.dtype != torch.bfloat16 or t.dim() != 2:
+        raise ValueError(f"{what} must be a bfloat16 matrix")
+    return t
+
+
+def linear_weight_grad(dz, x, stream=None):
+    """Weight gradient of a linear layer (bf16): dw = bf16(dz^T x), dz [m, n], x [m, k]."""
+    _bf16_matrix(dz, dz, "dz")
+    _bf16_matrix(x, dz, "x")
+    (m, n), k = dz.shape, x.shape[1]
+    if x.shape[0] != m:
+        raise ValueError("dz and x must have the same rows")
+    L = lib()
+    with _device_of(dz):   # launches go to the tensors' GPU
+        nbytes = L.lmbp_linear_grad_bytes(m, n, k, 0)
+        work = torch.empty(nbytes, dtype=torch.uint8, device=dz.device)
+        dw = torch.empty((n, k), dtype=torch.bfloat16, device=dz.device)
+        _check("linear_weight_grad", L.linear_weight_grad(BF16, m, n, k, _ptr(dz), _ptr(x), _ptr(dw), _ptr(work),
+                                                          nbytes, _stream(dz, stream)))
+    return dw
+
+
+def linear_act_bwd(dy, codes, x, act="gelu", weight_grad=True, stream=None):
+    """Backward of linear_act_fwd up to the input's product (bf16): returns (dz, dw, db),
+    dz = dy * slope[code], dw = bf16(dz^T x) (None without weight_grad), db = bf16 of the
+    column sums of dz. dy [m, n], x [m, k]."""
+    if act not in ("gelu", "silu"):
+        raise ValueError("act must be 'gelu' or 'silu'")
+    _bf16_matrix(dy, dy, "dy")
+    _bf16_matrix(x, dy, "x")
+    _on(codes, dy, "codes")
+    (m, n), k = dy.shape, x.shape[1]
+    if x.shape[0] != m:
+        raise ValueError("dy and x must have the same rows")
+    if codes.dtype != torch.int32 or codes.numel() < codes_words(m * n):
+        raise ValueError("codes must be the int32 buffer written by the forward")
+    L = lib()
+    with _device_of(dy):   # launches go to the tensors' GPU
+        nbytes = L.lmbp_linear_grad_bytes(m, n, k, 1)
+        work = torch.empty(nbytes, dtype=torch.uint8, device=dy.device)
+        dz = torch.empty_like(dy)
+        dw = torch.empty((n, k), dtype=torch.bfloat16, device=dy.device) if weight_grad else None
+        db = torch.empty(n, dtype=torch.bfloat16, device=dy.device)
+        _check("linear_act_bwd", L.linear_act_bwd(ACT_GELU if act == "gelu" else ACT_SILU, BF16, m, n, k, _ptr(dy),
+                                                  _ptr(codes), _ptr(x), _ptr(dz),
+                                                  _ptr(dw) if dw is not None else None, _ptr(db), _ptr(work),
+                                                  nbytes, _stream(dy, stream)))
+    return dz, dw, db
 
 
 def linear_swiglu_fwd(x, w_gate, w_up, h=None, s=None, u=None, codes=None, g=None, store_g=False,

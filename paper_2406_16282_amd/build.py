@@ -17,7 +17,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(HERE, "liblmbp.so")
 SOURCES = ("lmbp_api.hip", "act_kernels.hip", "norm_kernels.hip", "stepact_kernels.hip",
-           "linear_kernels.hip")
+           "linear_kernels.hip", "linear_grad_kernels.hip")
 ARCH = "gfx950"
 
 COMMON_FLAGS = [

@@ -299,6 +299,50 @@ lmbp_status linear_swiglu_fwd_impl(lmbp_dtype dt, int64_t m, int64_t n, int64_t 
                                               static_cast<hipStream_t>(stream)));
 }
 
+// Backward of a fused linear layer's parameters: dz given (dy == NULL) or computed here.
+lmbp_status linear_grad_impl(bool with_act, lmbp_act act, lmbp_dtype dt, int64_t m, int64_t n, int64_t k,
+                             const void* dy, const uint32_t* codes, const void* x, const void* dz_in,
+                             void* dz_out, void* dw, void* db, void* workspace, int64_t workspace_bytes,
+                             void* stream) {
+  if (!known_dtype(dt) || dt != LMBP_BF16) return LMBP_EDTYPE;
+  if (act != LMBP_ACT_GELU && act != LMBP_ACT_SILU) return LMBP_EINVAL;
+  const int64_t lim = int64_t(1) << 24;
+  if (m < 0 || n < 0 || k < 0 || m >= (int64_t(1) << 31) || n > lim || k > lim) return LMBP_EINVAL;
+  if (n % 16 != 0 || k % 8 != 0) return LMBP_EINVAL;
+  if (n == 0) return LMBP_OK;
+  const void* dz = with_act ? dz_out : dz_in;
+  const bool grad = dw != nullptr && k > 0;
+  if (m > 0 && (!dz || (grad && !x) || (with_act && (!dy || !codes)))) return LMBP_EINVAL;
+  if (!with_act && k > 0 && !dw) return LMBP_EINVAL;
+  const void* sixteen[] = {dy, x, dz, dw, workspace};
+  for (const void* p : sixteen)
+    if (p && !aligned(p, 16)) return LMBP_EINVAL;
+  if ((db && !aligned(db, 2)) || (codes && !aligned(codes, 4))) return LMBP_EINVAL;
+  const uint64_t need = lmbp::linear_grad_workspace(m, n, k, db != nullptr);
+  if (need > 0 && (!workspace || workspace_bytes < 0 || uint64_t(workspace_bytes) < need)) return LMBP_EINVAL;
+  const uint64_t mn = uint64_t(m) * uint64_t(n) * 2, mk = uint64_t(m) * uint64_t(k) * 2;
+  const Span sdw = span(dw, grad ? uint64_t(n) * uint64_t(k) * 2 : 0);
+  const Span outs[4] = {sdw, span(db, db ? uint64_t(n) * 2 : 0), span(workspace, need),
+                        span(dz_out, with_act && dz_out ? mn : 0)};
+  const Span ins[4] = {span(dy, dy ? mn : 0), span(codes, codes ? lmbp_codes_bytes(m * n) : 0),
+                       span(x, grad && x ? mk : 0), span(dz_in, dz_in ? mn : 0)};
+  for (int i = 0; i < 4; ++i) {
+    for (int j = i + 1; j < 4; ++j)
+      if (overlaps(outs[i], outs[j])) return LMBP_EOVERLAP;
+    for (const Span& in : ins)
+      if (overlaps(outs[i], in)) return LMBP_EOVERLAP;
+  }
+  const int a = act == LMBP_ACT_GELU ? lmbp::kGelu : lmbp::kSilu;
+  if (with_act && db == nullptr && m > 0) {
+    const hipError_t e = lmbp::launch_act_bwd(a, true, m * n, dy, codes, dz_out, true,
+                                              static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return from_hip(e);
+  }
+  return from_hip(lmbp::launch_linear_grad(a, m, n, k, dy, codes, x, const_cast<void*>(dz),
+                                           grad ? dw : nullptr, db, workspace,
+                                           static_cast<hipStream_t>(stream)));
+}
+
 // The norm-in-front forms: x [m x k] is MS-RMSNorm's input, z [m x k] and rstd [m] its
 // outputs; the rest as for the plain forms. k >= 8 (a norm needs a row).
 lmbp_status check_norm_in_front(int64_t m, int64_t n, int64_t k, float eps, const void* x,
@@ -430,6 +474,23 @@ lmbp_status reswiglu2_fwd(lmbp_dtype dt, int64_t n, const void* g, const void* u
 lmbp_status reswiglu2_bwd(lmbp_dtype dt, int64_t n, const void* dh, const void* u, const void* s,
                           const uint32_t* codes, void* dg, void* du, void* stream) {
   return glu_bwd(dt, n, dh, u, s, codes, dg, du, stream);
+}
+
+size_t lmbp_linear_grad_bytes(int64_t m, int64_t n, int64_t k, int bias) {
+  if (m < 0 || n <= 0 || k < 0 || n > (int64_t(1) << 24) || k > (int64_t(1) << 24)) return 0;
+  return lmbp::linear_grad_workspace(m, n, k, bias != 0);
+}
+lmbp_status linear_weight_grad(lmbp_dtype dt, int64_t m, int64_t n, int64_t k, const void* dz,
+                               const void* x, void* dw, void* workspace, int64_t workspace_bytes,
+                               void* stream) {
+  return linear_grad_impl(false, LMBP_ACT_GELU, dt, m, n, k, nullptr, nullptr, x, dz, nullptr, dw, nullptr,
+                          workspace, workspace_bytes, stream);
+}
+lmbp_status linear_act_bwd(lmbp_act act, lmbp_dtype dt, int64_t m, int64_t n, int64_t k,
+                           const void* dy, const uint32_t* codes, const void* x, void* dz, void* dw,
+                           void* db, void* workspace, int64_t workspace_bytes, void* stream) {
+  return linear_grad_impl(true, act, dt, m, n, k, dy, codes, x, nullptr, dz, dw, db, workspace,
+                          workspace_bytes, stream);
 }
 
 size_t lmbp_stepact_codes_bytes(int bits, int64_t n) {

@@ -9,8 +9,8 @@
   linear layer saves as its input, so autograd keeps one copy (memory sharing).
 * ``LinearReGELU2`` / ``LinearReSiLU2``: a bf16 linear layer followed by the activation,
   forward fused into one kernel (the pre-activation is never stored); saves x (for the
-  weight gradient) and the codes. Backward: dz = dy * slope[code] by the activation
-  kernel, then the two products of a linear layer's backward (library GEMMs).
+  weight gradient) and the codes. Backward: dz = dy * slope[code] with the bias gradient
+  in one kernel, the weight gradient in another, the input's product by a library GEMM.
 * ``LinearReSwiGLU2``: the LLaMA MLP's gate and up projections with SwiGLU, forward fused
   in one kernel (g never stored); backward through the SwiGLU activation backward and
   the linear layers' products.
@@ -18,9 +18,9 @@
   that consume its output, W~ = W diag(alpha), b~ = W beta + b (Sec. 5.2), and returns
   the parameter-free MS norm to use in its place.
 
-Every forward and backward runs in the HIP kernels through ``binding``, except the two
-matrix products of the fused linear layer's backward (torch's library GEMMs) and the
-one-time weight merge.
+Every forward and backward runs in the HIP kernels through ``binding``, except the
+product of the fused linear layers' backward for the input (torch's library GEMM) and
+the one-time weight merge.
 """
 
 import torch
@@ -82,6 +82,20 @@ class _MSNorm(torch.autograd.Function):
         return bwd(_flat(dz), z, rstd), None, None
 
 
+def _in_kernels(dz, x2):
+    """Whether the parameters' gradients can come from the library's kernels: not when the
+    backward pass is itself being recorded (create_graph: torch's products then carry the
+    graph), nor for tensors that a saved-tensor hook gave back in another layout."""
+    return (not torch.is_grad_enabled() and dz.is_contiguous() and x2.is_contiguous()
+            and dz.dtype == x2.dtype == torch.bfloat16 and dz.device == x2.device
+            and dz.data_ptr() % 16 == 0 and x2.data_ptr() % 16 == 0
+            and 0 < dz.shape[1] <= 1 << 24 and 0 < x2.shape[1])
+
+
+def _weight_grad(dz, x2):
+    return binding.linear_weight_grad(dz, x2) if _in_kernels(dz, x2) else dz.t().mm(x2)
+
+
 class _LinearAct(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, bias, which):
@@ -97,13 +111,17 @@ class _LinearAct(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy):
         x2, weight, codes = ctx.saved_tensors
-        bwd = binding.regelu2_bwd if ctx.which == "gelu" else binding.resilu2_bwd
-        dz = bwd(_flat(dy).reshape(-1, weight.shape[0]), codes)
-        # The two products of a linear layer's backward, as torch's own linear layer forms
-        # them (2-D GEMMs; the transposed left operand is read in place by the library).
-        dx = (dz @ weight).reshape(ctx.x_shape) if ctx.needs_input_grad[0] else None
-        dw = dz.t().mm(x2) if ctx.needs_input_grad[1] else None
-        db = dz.sum(0, dtype=torch.float32).to(dz.dtype) if ctx.has_bias and ctx.needs_input_grad[2] else None
+        dy = _flat(dy).reshape(-1, weight.shape[0])
+        need_x, need_w, need_b, _ = ctx.needs_input_grad
+        need_b = ctx.has_bias and need_b
+        if need_b and _in_kernels(dy, x2):
+            dz, dw, db = binding.linear_act_bwd(dy, codes, x2, ctx.which, weight_grad=need_w)
+        else:
+            dz = (binding.regelu2_bwd if ctx.which == "gelu" else binding.resilu2_bwd)(dy, codes)
+            dw = _weight_grad(dz, x2) if need_w else None
+            db = dz.sum(0, dtype=torch.float32).to(dz.dtype) if need_b else None
+        # The input's product as torch's own linear layer forms it (a 2-D library GEMM).
+        dx = (dz @ weight).reshape(ctx.x_shape) if need_x else None
         return dx, dw, db, None
 
 
@@ -142,9 +160,10 @@ class _LinearSwiGLU(torch.autograd.Function):
     def backward(ctx, dh):
         x2, w_gate, w_up, s, u, codes = ctx.saved_tensors
         dg, du = binding.reswiglu2_bwd(_flat(dh).reshape(-1, w_gate.shape[0]), u, s, codes)
-        dx = torch.addmm(dg @ w_gate, du, w_up).reshape(ctx.x_shape) if ctx.needs_input_grad[0] else None
-        dwg = dg.t().mm(x2) if ctx.needs_input_grad[1] else None
-        dwu = du.t().mm(x2) if ctx.needs_input_grad[2] else None
+        # the second product is added in place (out of place copies the first one before)
+        dx = (dg @ w_gate).addmm_(du, w_up).reshape(ctx.x_shape) if ctx.needs_input_grad[0] else None
+        dwg = _weight_grad(dg, x2) if ctx.needs_input_grad[1] else None
+        dwu = _weight_grad(du, x2) if ctx.needs_input_grad[2] else None
         return dx, dwg, dwu
 
 

@@ -1,0 +1,91 @@
+"""Parameter gradients of the fused linear layers: dW = dz^T x in every tile configuration
+and with the rows split or whole, ragged in every dimension, and the activation backward
+with the bias gradient. Inputs of the products are small integers times powers of two, so
+that every fp32 sum is exact in any order and dW must equal the rounding of torch's."""
+
+import pytest
+
+torch = pytest.importorskip("torch")
+import paper_2406_16282_amd as lmbp  # noqa: E402
+from paper_2406_16282_amd import nn as lnn  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dyadic(shape, exp, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return torch.randint(-8, 9, shape, generator=g, device=DEV).float() * 2.0 ** exp
+
+
+# rows x output features x input features; the comments name the tile and the shares of rows
+SHAPES = [
+    (0, 32, 16), (1, 16, 8), (63, 144, 264), (65, 400, 136), (197, 3072, 768),   # 128 x 128, whole
+    (700, 272, 136), (3001, 272, 520), (9001, 272, 264),                         # split
+    (4100, 528, 1032), (5000, 3072, 768), (6001, 1040, 520),
+    (333, 11008, 4104), (130, 11024, 4104), (1030, 8208, 2056), (1999, 5632, 2048),
+    (2048, 11008, 4096), (12609, 3072, 776),                                     # 256 x 256, whole and split
+]
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+def test_weight_grad_exact(m, n, k):
+    print(f"[grad] {m} {n} {k}", flush=True)
+    dz, x = dyadic((m, n), -3, 1), dyadic((m, k), -4, 2)
+    dw = lmbp.linear_weight_grad(dz.bfloat16(), x.bfloat16())
+    assert torch.equal(dw, (dz.t() @ x).bfloat16())
+
+
+@pytest.mark.parametrize("act", ["gelu", "silu"])
+@pytest.mark.parametrize("m,n,k", [(0, 32, 16), (1, 16, 8), (64, 528, 16), (129, 1040, 24), (3001, 272, 520),
+                                   (700, 3072, 768)])
+def test_act_bwd_with_bias(m, n, k, act):
+    """dz is the activation backward's, dw the product's of that dz; db is the rounding of
+    an fp32 sum of m values: within m 2^-24 of their absolute sum, plus one rounding (2^-8)."""
+    print(f"[grad] act {m} {n} {k} {act}", flush=True)
+    pre, dy, x = dyadic((m, n), -1, 1).bfloat16(), dyadic((m, n), -6, 2).bfloat16(), dyadic((m, k), -4, 3).bfloat16()
+    fwd, bwd = (lmbp.regelu2_fwd, lmbp.regelu2_bwd) if act == "gelu" else (lmbp.resilu2_fwd, lmbp.resilu2_bwd)
+    codes = fwd(pre)[1]
+    dz, dw, db = lmbp.linear_act_bwd(dy, codes, x, act)
+    ref = bwd(dy, codes)
+    assert torch.equal(dz.view(torch.int16), ref.view(torch.int16))
+    assert torch.equal(dw, lmbp.linear_weight_grad(ref, x))
+    exact, size = ref.double().sum(0), ref.double().abs().sum(0)
+    assert ((db.double() - exact).abs() <= exact.abs() * 2.0 ** -8 + size * m * 2.0 ** -24 * 1.01).all()
+    dz2, none, db2 = lmbp.linear_act_bwd(dy, codes, x, act, weight_grad=False)
+    assert none is None and torch.equal(dz2, dz) and torch.equal(db2, db)
+
+
+@pytest.mark.parametrize("needs", [(True, True, True), (False, True, True), (True, False, True), (True, True, False)])
+def test_module_gradients_against_recorded_backward(needs):
+    """The kernels' gradients against those of a recorded backward (create_graph), which
+    are torch's products of the same dz: one rounding apart at most."""
+    layer = lnn.LinearReGELU2(264, 272, device=DEV)
+    x = torch.randn(3, 67, 264, device=DEV, dtype=torch.bfloat16)
+    dy = torch.randn(3, 67, 272, device=DEV, dtype=torch.bfloat16)
+    x.requires_grad_(needs[0])
+    layer.weight.requires_grad_(needs[1])
+    layer.bias.requires_grad_(needs[2])
+    wrt = [t for t in (x, layer.weight, layer.bias) if t.requires_grad]
+    got = torch.autograd.grad(layer(x), wrt, dy)
+    ref = torch.autograd.grad(layer(x), wrt, dy, create_graph=True)
+    for a, r in zip(got, ref):
+        d = (a.double() - r.double()).abs()
+        assert (d <= r.double().abs() * 2.0 ** -7 + 1e-3 * r.double().square().mean().sqrt()).all()
+
+
+def test_saved_tensor_hooks_may_change_the_layout():
+    layer = lnn.LinearReSiLU2(64, 48, device=DEV)
+    x = torch.randn(33, 64, device=DEV, dtype=torch.bfloat16, requires_grad=True)
+    dy = torch.randn(33, 48, device=DEV, dtype=torch.bfloat16)
+    ref = torch.autograd.grad(layer(x), [x, layer.weight, layer.bias], dy)
+
+    def unpack(t):   # the same values in another layout
+        return t.t().contiguous().t() if t.dim() == 2 else t
+
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, unpack):
+        y = layer(x)
+        got = torch.autograd.grad(y, [x, layer.weight, layer.bias], dy)
+    for a, r in zip(got, ref):
+        assert torch.allclose(a.float(), r.float(), rtol=2.0 ** -6, atol=1e-2)
