@@ -308,17 +308,16 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void grad_weight_kernel(
 }
 
 // dz = dy * slope[code] as the activation kernels compute it, and the sums of the rounded dz
-// over blocks of 64 rows, per column (fp32): the read of dz that a separate sum would take
-// is saved (12608 x 3072: 28 us for that sum, and this kernel takes no longer than the one
-// without sums). A wave takes 512 columns, 8 per lane, of 16 rows; the four waves of a block
-// add theirs in LDS. Needs 16-byte aligned tensors and N % 16 == 0.
-constexpr int kColRows = 64;
+// over blocks of 32 rows, per column (fp32): the read of dz that a separate sum would take
+// is saved. A wave takes 512 columns, 8 per lane, of 8 rows, all requested at once; the four
+// waves of a block add theirs in LDS. Needs 16-byte aligned tensors and N % 16 == 0.
+constexpr int kColRows = 32;
 template <int ACT>
 __global__ __launch_bounds__(256) void act_bwd_cols_kernel(const void* dy, const uint32_t* __restrict__ codes,
                                                            void* dz, float* __restrict__ sums, int64_t M,
                                                            int64_t N) {
   using A = ActOf<ACT>;
-  constexpr int kRows = kColRows / 4, kAhead = 8;
+  constexpr int kRows = kColRows / 4;
   __shared__ float part[4][8][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_in_block();
@@ -326,29 +325,26 @@ __global__ __launch_bounds__(256) void act_bwd_cols_kernel(const void* dy, const
   const int64_t row0 = int64_t(blockIdx.x) * kColRows + wave * kRows;
   const bool in_col = col < N;
   float sum[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  u32x4 v[kRows];
+  uint32_t w[kRows];
 #pragma unroll
-  for (int r0 = 0; r0 < kRows; r0 += kAhead) {
-    u32x4 v[kAhead];
-    uint32_t w[kAhead];
+  for (int r = 0; r < kRows; ++r) {
+    const int64_t at = (row0 + r) * N + col;
+    const bool in = in_col && row0 + r < M;
+    v[r] = in ? ldg16<true>(dy, at / 8) : u32x4{0u, 0u, 0u, 0u};
+    w[r] = in ? codes[at / 16] >> (16 * (lane & 1)) : 0u;
+  }
 #pragma unroll
-    for (int r = 0; r < kAhead; ++r) {
-      const int64_t at = (row0 + r0 + r) * N + col;
-      const bool in = in_col && row0 + r0 + r < M;
-      v[r] = in ? ldg16<true>(dy, at / 8) : u32x4{0u, 0u, 0u, 0u};
-      w[r] = in ? codes[at / 16] >> (16 * (lane & 1)) : 0u;
-    }
+  for (int r = 0; r < kRows; ++r) {
+    float f[8];
+    BF16::unpack(v[r], f);
 #pragma unroll
-    for (int r = 0; r < kAhead; ++r) {
-      float f[8];
-      BF16::unpack(v[r], f);
+    for (int e = 0; e < 8; ++e) f[e] = f[e] * seg_slope<A>((w[r] >> (2 * e)) & 3u);
+    const u32x4 out = BF16::pack(f);
+    if (in_col && row0 + r < M) stg16(dz, ((row0 + r) * N + col) / 8, out);
+    BF16::unpack(out, f);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) f[e] = f[e] * seg_slope<A>((w[r] >> (2 * e)) & 3u);
-      const u32x4 out = BF16::pack(f);
-      if (in_col && row0 + r0 + r < M) stg16(dz, ((row0 + r0 + r) * N + col) / 8, out);
-      BF16::unpack(out, f);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sum[e] += f[e];
-    }
+    for (int e = 0; e < 8; ++e) sum[e] += f[e];
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) part[wave][e][lane] = sum[e];
@@ -363,23 +359,29 @@ __global__ __launch_bounds__(256) void act_bwd_cols_kernel(const void* dy, const
 
 // The second passes, in one launch. The first dw_blocks blocks: dw = bf16(sum of the
 // splits' partial sums, in split order), 8 values per thread. The others: db = bf16(sum of
-// the row blocks' column sums, in a fixed order), 64 columns per block.
+// the row blocks' column sums, in a fixed order), 16 columns per block, 16 threads to a
+// column, each with four loads in flight (one thread to a column and a quarter of the rows
+// was a chain of 50 loads: 23 us).
 __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ part, uint16_t* dw, int64_t n,
                                                           int splits, int64_t dw_blocks,
                                                           const float* __restrict__ sums, uint16_t* db,
                                                           int64_t cols, int64_t row_blocks) {
-  __shared__ float red[4][kWave];
+  __shared__ float red[16][16];
   if (int64_t(blockIdx.x) >= dw_blocks) {
-    const int64_t col = (int64_t(blockIdx.x) - dw_blocks) * kWave + (threadIdx.x & (kWave - 1));
-    const int q = threadIdx.x / kWave;
-    float t = 0.0f;
-    if (col < cols)
-      for (int64_t b = q; b < row_blocks; b += 4) t += sums[b * cols + col];
-    red[q][threadIdx.x & (kWave - 1)] = t;
+    const int c = threadIdx.x % 16, q = threadIdx.x / 16;
+    const int64_t col = (int64_t(blockIdx.x) - dw_blocks) * 16 + c;   // cols is a multiple of 16
+    float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int64_t b = q; b < row_blocks; b += 64) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] += b + 16 * u < row_blocks ? sums[(b + 16 * u) * cols + col] : 0.0f;
+    }
+    red[q][c] = (t[0] + t[1]) + (t[2] + t[3]);
     __syncthreads();
-    if (q == 0 && col < cols) {
-      const int l = threadIdx.x;
-      BF16::store1(db, col, ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l]);
+    if (q == 0) {
+      float sum = red[0][c];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) sum += red[r][c];
+      BF16::store1(db, col, sum);
     }
     return;
   }
@@ -537,7 +539,7 @@ hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const vo
         : plan.tile == 1 ? launch_tile<MidTile>(a, plan, dev, cus, s) : launch_tile<SmallTile>(a, plan, dev, cus, s);
     if (e != hipSuccess) return e;
   }
-  const int64_t dw_blocks = split ? (N * K / 8 + 255) / 256 : 0, db_blocks = db != nullptr ? (N + kWave - 1) / kWave : 0;
+  const int64_t dw_blocks = split ? (N * K / 8 + 255) / 256 : 0, db_blocks = db != nullptr ? N / 16 : 0;
   if (dw_blocks + db_blocks > 0x7fffffff) return hipErrorInvalidValue;
   if (dw_blocks + db_blocks > 0) {
     hipLaunchKernelGGL(grad_reduce_kernel, dim3(unsigned(dw_blocks + db_blocks)), dim3(256), 0, s, part,
