@@ -5,10 +5,16 @@ contiguity, their device pointers and the current HIP stream are passed to the C
 ABI, and a non-OK status raises ``LmbpError``. Every step of the computation runs
 in the library's HIP kernels. There is no fallback: if liblmbp.so has not been
 built, the first call raises.
+
+The common form of a call (plain tensors on the current device, no output or stream
+given) does its marshalling in native code (csrc/fastcall.cpp); that code declines
+anything else, which then takes the path below with its errors.
 """
 
 import contextlib
 import ctypes
+import importlib.machinery
+import importlib.util
 import math
 import os
 
@@ -16,6 +22,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "liblmbp.so")
+FAST_PATH = os.path.join(HERE, "_fastcall.so")
 
 FP32, BF16 = 0, 1
 OK, EINVAL, EDTYPE, EOVERLAP, EHIP = 0, 1, 2, 3, 4
@@ -33,6 +40,10 @@ class LmbpError(RuntimeError):
         super().__init__(f"{op}: status {status}: {message}")
         self.status = status
 
+
+# torch's own accessor of the current stream's raw handle (a few hundred ns, against ~2 us
+# for building a torch.cuda.Stream object); the public call is the fallback.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 _lib = None
 
@@ -93,8 +104,37 @@ def lib():
     L.linear_act_bwd.restype = i32
     L.lmbp_copy.argtypes = [vp, vp, i64, vp]
     L.lmbp_copy.restype = i32
+    _bind_fast(L)
     _lib = L
     return L
+
+
+# The native calls and the addresses of the library's functions, set with the library.
+_fast = None
+_address = {}
+
+
+def _bind_fast(L):
+    global _fast
+    if _raw_stream is None:
+        return   # no raw handle of the current stream: every call takes the Python path
+    if not os.path.exists(FAST_PATH):
+        raise RuntimeError(
+            f"{FAST_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
+    loader = importlib.machinery.ExtensionFileLoader("_fastcall", FAST_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fastcall", loader))
+    loader.exec_module(module)
+    module.bind(_raw_stream)
+    for name in (*ACT_OPS, *NORM_OPS, *GLU_OPS, "linear_act_fwd", "linear_swiglu_fwd"):
+        _address[name] = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+    _fast = module
+
+
+def _done(op, out):
+    """A native call's result, or its status raised."""
+    if type(out) is int:
+        _check(op, out)
+    return out
 
 
 def strerror(status):
@@ -143,11 +183,6 @@ def _on(t, ref, what):
     return t
 
 
-# torch's own accessor of the current stream's raw handle (a few hundred ns, against ~2 us
-# for building a torch.cuda.Stream object); the public call is the fallback.
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
 def _stream(t, stream):
     """The HIP stream to launch on: the tensors' current stream by default, else a
     torch.cuda.Stream of the same device or a raw stream handle."""
@@ -194,6 +229,10 @@ def _codes_out(n, device, codes):
 
 
 def _act_fwd(op, x, y, codes, stream):
+    if _fast is not None and y is None and codes is None and stream is None:
+        out = _fast.act_fwd(_address[op], x)
+        if out is not None:
+            return _done(op, out)
     _dev(x, "x")
     dt = _dtype_code(x)
     y = _like(x, y, "y")
@@ -204,6 +243,10 @@ def _act_fwd(op, x, y, codes, stream):
 
 
 def _act_bwd(op, dy, codes, dx, stream):
+    if _fast is not None and dx is None and stream is None:
+        out = _fast.act_bwd(_address[op], dy, codes)
+        if out is not None:
+            return _done(op, out)
     _dev(dy, "dy")
     dt = _dtype_code(dy)
     _on(codes, dy, "codes")
@@ -244,6 +287,10 @@ def _same(t, ref, what):
 
 def reswiglu2_fwd(g, u, h=None, s=None, codes=None, stream=None):
     """ReSiLU2 in a SwiGLU product: returns (h = SiLU(g) * u, s = SiLU(g), codes of g)."""
+    if _fast is not None and h is None and s is None and codes is None and stream is None:
+        out = _fast.glu_fwd(_address["reswiglu2_fwd"], g, u)
+        if out is not None:
+            return _done("reswiglu2_fwd", out)
     _dev(g, "g")
     dt = _dtype_code(g)
     _same(u, g, "u")
@@ -258,6 +305,10 @@ def reswiglu2_fwd(g, u, h=None, s=None, codes=None, stream=None):
 
 def reswiglu2_bwd(dh, u, s, codes, dg=None, du=None, stream=None):
     """Backward of reswiglu2_fwd: returns (dg = dh * u * slope[code], du = dh * s)."""
+    if _fast is not None and dg is None and du is None and stream is None:
+        out = _fast.glu_bwd(_address["reswiglu2_bwd"], dh, u, s, codes)
+        if out is not None:
+            return _done("reswiglu2_bwd", out)
     _dev(dh, "dh")
     dt = _dtype_code(dh)
     _same(u, dh, "u")
@@ -330,6 +381,10 @@ def _rows_cols(t):
 
 
 def _norm_fwd(op, x, eps, z, rstd, stream):
+    if _fast is not None and z is None and rstd is None and stream is None:
+        out = _fast.norm_fwd(_address[op], x, eps)
+        if out is not None:
+            return _done(op, out)
     _dev(x, "x")
     dt = _dtype_code(x)
     rows, cols = _rows_cols(x)
@@ -347,6 +402,10 @@ def _norm_fwd(op, x, eps, z, rstd, stream):
 
 
 def _norm_bwd(op, dz, z, rstd, dx, stream):
+    if _fast is not None and dx is None and stream is None:
+        out = _fast.norm_bwd(_address[op], dz, z, rstd)
+        if out is not None:
+            return _done(op, out)
     _dev(dz, "dz")
     _on(z, dz, "z")
     _on(rstd, dz, "rstd")
@@ -402,6 +461,10 @@ def linear_act_fwd(x, w, bias=None, act="gelu", y=None, codes=None, z=None, stor
     None. Returns (y, codes) or, with store_z (or a z tensor given), (y, codes, z)."""
     if act not in ("gelu", "silu"):
         raise ValueError("act must be 'gelu' or 'silu'")
+    if _fast is not None and y is None and codes is None and z is None and not store_z and stream is None:
+        out = _fast.linear_act_fwd(_address["linear_act_fwd"], ACT_GELU if act == "gelu" else ACT_SILU, x, w, bias)
+        if out is not None:
+            return _done("linear_act_fwd", out)
     _dev(x, "x")
     _on(w, x, "w")
     if x.dtype != torch.bfloat16 or w.dtype != torch.bfloat16:
@@ -495,6 +558,11 @@ def linear_swiglu_fwd(x, w_gate, w_up, h=None, s=None, u=None, codes=None, g=Non
     """Fused LLaMA MLP input side (bf16): g = bf16(x Wg^T), u = bf16(x Wu^T),
     h = SiLU(g) * u, s = SiLU(g), codes of g. Returns (h, s, u, codes) or, with store_g
     (or a g tensor given), (h, s, u, codes, g)."""
+    if (_fast is not None and h is None and s is None and u is None and codes is None and g is None and not store_g
+            and stream is None):
+        out = _fast.linear_swiglu_fwd(_address["linear_swiglu_fwd"], x, w_gate, w_up)
+        if out is not None:
+            return _done("linear_swiglu_fwd", out)
     for t, nm in ((x, "x"), (w_gate, "w_gate"), (w_up, "w_up")):
         _on(t, x, nm)
         if t.dtype != torch.bfloat16:
