@@ -667,14 +667,20 @@ hipError_t launch_tile(LinArgs a, int dev, int cus, hipStream_t s) {
 }
 
 // Estimated time of a tile configuration, in us: full rounds of the resident blocks and a
-// partial one, in which a CU with fewer blocks is faster. The coefficients are a
-// least-squares fit (relative error 7 to 10% rms) to the measured times of each
-// configuration on M = 16 .. 12608 rows of seven layers (K x N = 512 x 2048, 768 x 3072,
-// 1000 x 4000, 1024 x 4096 with GELU; 2048 x 5632, 4096 x 11008, 5120 x 13824 gated), 256
-// CUs. Taking the configuration that the model prefers was within 0.6% of the fastest one
-// on average (at worst 13%). The single rule used before (256 x 256 tiles from four rounds
-// of them on, else 128 x 128) was 18% slower on average: 1024 rows of the 4096 x 11008
-// gated layer 213 us against 181, 2048 rows 416 against 302.
+// partial one, in which a CU with fewer blocks is faster. The coefficients are
+// least-squares fits (relative error 7 to 12% rms) to the measured times of each
+// configuration on 256 CUs: kLinearCost on M = 16 .. 12608 rows of layers from K x N =
+// 512 x 2048 to 1024 x 4096 with GELU and three gated ones, kGatedCost on M = 16 .. 4096
+// rows of six gated layers from 520 x 4112 to 5120 x 13824. The gated form has terms of
+// its own because its epilogue writes three tensors and the codes: a round of 64 x 128
+// tiles costs 9 us there beside its K steps, not 2. Its fit weighs a time by how near it is
+// to the layer's fastest, and that round is 3 us and the 128 x 256 one -1 us from its
+// least-squares value, in the middle of the range that gives the same choices. The choice
+// is 1.1% slower than the fastest configuration on average (one set of terms for both
+// forms: 2.6%, and 57 us where 46 were to be had at 2000 rows of 520 x 4112). The single
+// rule used before (256 x 256 tiles from four rounds of them on, else 128 x 128) was 18%
+// slower on average: 1024 rows of the 4096 x 11008 gated layer 213 us against 181, 2048
+// rows 416 against 302.
 struct Cost {
   float base, step_full, step_any, step_second, step_third, step_load, full, any, second;
 };
@@ -688,10 +694,17 @@ float cost(const LinArgs& a, int cus, const Cost& c) {
                          c.step_third * third + c.step_load * (float(rest) / float(slots));
   return c.base + float((a.K + kBK - 1) / kBK) * per_step + c.full * float(full) + c.any * any + c.second * second;
 }
-constexpr Cost kBigCost = {5.53f, 1.386f, 0.844f, 0.0f, 0.0f, 0.735f, 17.28f, 10.29f, 0.0f};
-constexpr Cost kMidCost = {10.13f, 1.567f, 0.739f, 0.241f, 0.0f, 0.901f, 14.30f, 0.33f, 5.46f};
-constexpr Cost kSmallCost = {4.51f, 1.027f, 0.468f, 0.257f, 0.0f, 0.569f, 6.06f, 0.21f, 0.96f};
-constexpr Cost kLowCost = {2.87f, 1.091f, 0.484f, 0.177f, 0.164f, 0.447f, 2.32f, 0.0f, 0.0f};
+struct TileCosts {
+  Cost big, mid, small, low;
+};
+constexpr TileCosts kLinearCost = {{5.53f, 1.386f, 0.844f, 0.0f, 0.0f, 0.735f, 17.28f, 10.29f, 0.0f},
+                                   {10.13f, 1.567f, 0.739f, 0.241f, 0.0f, 0.901f, 14.30f, 0.33f, 5.46f},
+                                   {4.51f, 1.027f, 0.468f, 0.257f, 0.0f, 0.569f, 6.06f, 0.21f, 0.96f},
+                                   {2.87f, 1.091f, 0.484f, 0.177f, 0.164f, 0.447f, 2.32f, 0.0f, 0.0f}};
+constexpr TileCosts kGatedCost = {{1.39f, 1.311f, 0.833f, 0.0f, 0.0f, 0.789f, 19.35f, 13.27f, 0.0f},
+                                  {0.0f, 1.366f, 0.842f, 0.149f, 0.0f, 0.831f, 21.57f, 6.72f, 8.18f},
+                                  {0.0f, 0.863f, 0.471f, 0.171f, 0.0f, 0.689f, 10.82f, 3.93f, 1.20f},
+                                  {1.20f, 0.963f, 0.601f, 0.125f, 0.302f, 0.271f, 8.88f, 0.0f, 1.46f}};
 
 // The same for the split-K form, fitted to 16 .. 512 rows of the same layers: a latency,
 // the chain of a wave's K steps, and the bytes that all blocks take in (per MB, 256 CUs).
@@ -729,8 +742,9 @@ hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
   int dev = 0, cus = 0;
   const hipError_t e = current_device(dev, cus);
   if (e != hipSuccess) return e;
-  const float big = cost<BigTile, GLU>(a, cus, kBigCost), mid = cost<MidTile, GLU>(a, cus, kMidCost);
-  const float small = cost<SmallTile, GLU>(a, cus, kSmallCost), low = cost<LowTile, GLU>(a, cus, kLowCost);
+  constexpr TileCosts c = GLU ? kGatedCost : kLinearCost;
+  const float big = cost<BigTile, GLU>(a, cus, c.big), mid = cost<MidTile, GLU>(a, cus, c.mid);
+  const float small = cost<SmallTile, GLU>(a, cus, c.small), low = cost<LowTile, GLU>(a, cus, c.low);
   const float rows16 = rows_cost<1, GLU>(a, cus, kRows16Cost), rows32 = rows_cost<2, GLU>(a, cus, kRows32Cost);
   const float tiled = std::min(std::min(big, mid), std::min(small, low));
   if (rows16 < tiled && rows16 <= rows32) return launch_rows<1, ACT, GLU, NORM>(a, s);

@@ -52,7 +52,7 @@ def test_plain(m, n, k, act):
 
 
 @pytest.mark.parametrize("m,n,k", [(1, 16, 8), (16, 11008, 520), (17, 48, 264), (29, 5632, 2056), (100, 80, 776),
-                                   (2, 16400, 1032), (700, 1552, 8), (4097, 4112, 8), (3001, 1040, 72),
+                                   (2, 16400, 1032), (129, 16400, 136), (700, 1552, 8), (4097, 4112, 8), (3001, 1040, 72),
                                    (1025, 3056, 72), (4097, 5648, 520), (1999, 5648, 776), (1999, 3088, 520),
                                    (2049, 3056, 520), (2048, 11008, 1032)])
 def test_gated(m, n, k):
