@@ -125,7 +125,8 @@ def _bind_fast(L):
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fastcall", loader))
     loader.exec_module(module)
     module.bind(_raw_stream)
-    for name in (*ACT_OPS, *NORM_OPS, *GLU_OPS, "linear_act_fwd", "linear_swiglu_fwd"):
+    for name in (*ACT_OPS, *NORM_OPS, *GLU_OPS, "linear_act_fwd", "linear_swiglu_fwd", "msrms_linear_act_fwd",
+                 "msrms_linear_swiglu_fwd"):
         _address[name] = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
     _fast = module
 
@@ -616,6 +617,12 @@ def msrms_linear_act_fwd(x, w, eps, bias=None, act="silu", y=None, codes=None, z
     (y, codes, z, rstd, pre) with pre the rounded pre-activation."""
     if act not in ("gelu", "silu"):
         raise ValueError("act must be 'gelu' or 'silu'")
+    if (_fast is not None and y is None and codes is None and z is None and rstd is None and pre is None
+            and not store_pre and stream is None):
+        out = _fast.norm_linear_act_fwd(_address["msrms_linear_act_fwd"], ACT_GELU if act == "gelu" else ACT_SILU,
+                                        x, w, eps, bias)
+        if out is not None:
+            return _done("msrms_linear_act_fwd", out)
     _dev(x, "x")
     _on(w, x, "w")
     if x.dtype != torch.bfloat16 or w.dtype != torch.bfloat16:
@@ -657,6 +664,11 @@ def msrms_linear_swiglu_fwd(x, w_gate, w_up, eps, h=None, s=None, u=None, codes=
     msrms_fwd; g, u = bf16(rstd (x W^T)); h = SiLU(g) u, s = SiLU(g), codes of g.
     Returns (h, s, u, codes, z, rstd) or, with store_g (or a g tensor given),
     (h, s, u, codes, z, rstd, g)."""
+    if (_fast is not None and h is None and s is None and u is None and codes is None and z is None and rstd is None
+            and g is None and not store_g and stream is None):
+        out = _fast.norm_linear_swiglu_fwd(_address["msrms_linear_swiglu_fwd"], x, w_gate, w_up, eps)
+        if out is not None:
+            return _done("msrms_linear_swiglu_fwd", out)
     for t, nm in ((x, "x"), (w_gate, "w_gate"), (w_up, "w_up")):
         _on(t, x, nm)
         if t.dtype != torch.bfloat16:

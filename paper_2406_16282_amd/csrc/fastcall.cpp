@@ -298,6 +298,69 @@ PyObject* linear_swiglu_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
+// (function, activation, x, w, eps, bias or None) -> (y, codes, z, rstd)
+PyObject* norm_linear_act_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  at::Tensor x, w, b;
+  int64_t m;
+  c10::SmallVector<int64_t, 6> shape;
+  if (n != 6 || !PyFloat_CheckExact(a[4]) || !plain(a[2], x) || !plain(a[3], w) || !layer(x, w, m, shape))
+    Py_RETURN_NONE;
+  if (a[5] != Py_None && (!plain(a[5], b) || b.scalar_type() != at::kBFloat16 || b.numel() != w.size(0) ||
+                          b.device() != x.device()))
+    Py_RETURN_NONE;
+  void* s;
+  if (!stream_of(x, s)) return nullptr;
+  const int act = int(PyLong_AsLong(a[1]));
+  at::Tensor y, codes, z, rstd;
+  const auto f = address<int (*)(int, int, int64_t, int64_t, int64_t, float, const void*, const void*, const void*,
+                                 void*, void*, void*, void*, void*, void*)>(a[0]);
+  int status;
+  {
+    NoGil released;
+    y = at::empty(shape, x.options());
+    z = at::empty(x.sizes(), x.options());
+    rstd = at::empty({m}, x.options().dtype(at::kFloat));
+    codes = words(code_words(m * w.size(0)), x);
+    status = f(act, kBf16, m, w.size(0), w.size(1), float(PyFloat_AS_DOUBLE(a[4])), x.data_ptr(), w.data_ptr(),
+               b.defined() ? b.data_ptr() : nullptr, y.data_ptr(), codes.data_ptr(), nullptr, z.data_ptr(),
+               rstd.data_ptr(), s);
+  }
+  return result(status, y, codes, z, rstd);
+  END_HANDLE_TH_ERRORS
+}
+
+// (function, x, w_gate, w_up, eps) -> (h, s, u, codes, z, rstd)
+PyObject* norm_linear_swiglu_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  at::Tensor x, wg, wu;
+  int64_t m;
+  c10::SmallVector<int64_t, 6> shape;
+  if (n != 5 || !PyFloat_CheckExact(a[4]) || !plain(a[1], x) || !plain(a[2], wg) || !plain(a[3], wu) ||
+      !layer(x, wg, m, shape) || !same(wu, wg) || wu.sizes() != wg.sizes())
+    Py_RETURN_NONE;
+  void* st;
+  if (!stream_of(x, st)) return nullptr;
+  at::Tensor h, s, u, codes, z, rstd;
+  const auto f = address<int (*)(int, int64_t, int64_t, int64_t, float, const void*, const void*, const void*, void*,
+                                 void*, void*, void*, void*, void*, void*, void*)>(a[0]);
+  int status;
+  {
+    NoGil released;
+    h = at::empty(shape, x.options());
+    s = at::empty(shape, x.options());
+    u = at::empty(shape, x.options());
+    z = at::empty(x.sizes(), x.options());
+    rstd = at::empty({m}, x.options().dtype(at::kFloat));
+    codes = words(code_words(m * wg.size(0)), x);
+    status = f(kBf16, m, wg.size(0), wg.size(1), float(PyFloat_AS_DOUBLE(a[4])), x.data_ptr(), wg.data_ptr(),
+               wu.data_ptr(), h.data_ptr(), s.data_ptr(), u.data_ptr(), codes.data_ptr(), nullptr, z.data_ptr(),
+               rstd.data_ptr(), st);
+  }
+  return result(status, h, s, u, codes, z, rstd);
+  END_HANDLE_TH_ERRORS
+}
+
 // (torch's raw-stream accessor)
 PyObject* bind(PyObject*, PyObject* accessor) {
   Py_INCREF(accessor);
@@ -308,7 +371,8 @@ PyObject* bind(PyObject*, PyObject* accessor) {
 #define LMBP_FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef kMethods[] = {LMBP_FAST(act_fwd), LMBP_FAST(act_bwd), LMBP_FAST(glu_fwd), LMBP_FAST(glu_bwd),
                           LMBP_FAST(norm_fwd), LMBP_FAST(norm_bwd), LMBP_FAST(linear_act_fwd),
-                          LMBP_FAST(linear_swiglu_fwd), {"bind", bind, METH_O, nullptr},
+                          LMBP_FAST(linear_swiglu_fwd), LMBP_FAST(norm_linear_act_fwd),
+                          LMBP_FAST(norm_linear_swiglu_fwd), {"bind", bind, METH_O, nullptr},
                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 

@@ -32,6 +32,9 @@ def calls(shape, dtype):
         yield "linear_act_fwd", (x, w)
         yield "linear_act_fwd", (x, w, torch.randn(48, device=DEV, dtype=dtype), "silu")
         yield "linear_swiglu_fwd", (x, w, w2)
+        yield "msrms_linear_act_fwd", (x, w, 1e-5)
+        yield "msrms_linear_act_fwd", (x, w, 1e-5, torch.randn(48, device=DEV, dtype=dtype), "gelu")
+        yield "msrms_linear_swiglu_fwd", (x, w, w2, 1e-5)
 
 
 def tensors(out):
@@ -75,6 +78,8 @@ def test_declined_forms_keep_their_errors():
             (ValueError, lambda: lmbp.msln_fwd(x[0, 0], 1e-6)), (ValueError, lambda: lmbp.msrms_bwd(x, z.float(), rstd)),
             (ValueError, lambda: lmbp.msrms_bwd(x, z, rstd.double())), (ValueError, lambda: lmbp.reswiglu2_fwd(x, z.float())),
             (TypeError, lambda: lmbp.linear_act_fwd(x.float(), x)), (ValueError, lambda: lmbp.linear_act_fwd(x, z[:, :8].contiguous())),
+            (TypeError, lambda: lmbp.msrms_linear_swiglu_fwd(x, x.float(), x, 1e-5)),
+            (ValueError, lambda: lmbp.msrms_linear_act_fwd(x, z[:, :8].contiguous(), 1e-5)),
             (lmbp.LmbpError, lambda: lmbp.linear_act_fwd(x, x)), (lmbp.LmbpError, lambda: lmbp.msln_fwd(x, -1.0))):
         with pytest.raises(kind):
             call()
