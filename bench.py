@@ -517,9 +517,9 @@ def linear_report(torch, lmbp, inputs, dev, reps):
     print(f"[bench] linear {name}: fused {t_fused:.1f} us ({tf:.0f} TFLOP/s), unfused "
           f"{t_unfused:.1f} us (two library GEMMs + SwiGLU activation)", file=sys.stderr, flush=True)
 
-    # MS-RMSNorm in front of the same gated layer: the norm's statistics pass plus the GEMM
-    # that also writes the norm's output z, against the norm kernel followed by the fused
-    # gated layer on z (the same layer, the same saved z and rstd).
+    # MS-RMSNorm in front of the same gated layer: the norm kernel plus the GEMM on x with
+    # rstd in its epilogue, against the norm kernel followed by the fused gated layer on z
+    # (the same layer, the same saved z and rstd).
     name = "llama7b_msrms_mlp_swiglu_bf16"
     eps = float(np.float32(1e-5))
     xn = T(inputs.normal((m, k), 1.0, "bf16", tensor_id=inputs.NORM_X))
