@@ -206,6 +206,18 @@ def _device_of(t):
     return torch.cuda.device(t.device)
 
 
+def _workspace(nbytes, t, stream):
+    """Scratch memory of a launch on ``stream``, allocated on that stream: it is dropped when
+    the call returns, and the caching allocator then hands it out again only behind the
+    work of the stream that it belongs to."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=t.device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(int(stream), device=t.device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=t.device)
+
+
 def _ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
@@ -519,10 +531,11 @@ def linear_weight_grad(dz, x, stream=None):
     L = lib()
     with _device_of(dz):   # launches go to the tensors' GPU
         nbytes = L.lmbp_linear_grad_bytes(m, n, k, 0)
-        work = torch.empty(nbytes, dtype=torch.uint8, device=dz.device)
+        handle = _stream(dz, stream)
+        work = _workspace(nbytes, dz, stream)
         dw = torch.empty((n, k), dtype=torch.bfloat16, device=dz.device)
         _check("linear_weight_grad", L.linear_weight_grad(BF16, m, n, k, _ptr(dz), _ptr(x), _ptr(dw), _ptr(work),
-                                                          nbytes, _stream(dz, stream)))
+                                                          nbytes, handle))
     return dw
 
 
@@ -543,14 +556,15 @@ def linear_act_bwd(dy, codes, x, act="gelu", weight_grad=True, stream=None):
     L = lib()
     with _device_of(dy):   # launches go to the tensors' GPU
         nbytes = L.lmbp_linear_grad_bytes(m, n, k, 1)
-        work = torch.empty(nbytes, dtype=torch.uint8, device=dy.device)
+        handle = _stream(dy, stream)
+        work = _workspace(nbytes, dy, stream)
         dz = torch.empty_like(dy)
         dw = torch.empty((n, k), dtype=torch.bfloat16, device=dy.device) if weight_grad else None
         db = torch.empty(n, dtype=torch.bfloat16, device=dy.device)
         _check("linear_act_bwd", L.linear_act_bwd(ACT_GELU if act == "gelu" else ACT_SILU, BF16, m, n, k, _ptr(dy),
                                                   _ptr(codes), _ptr(x), _ptr(dz),
                                                   _ptr(dw) if dw is not None else None, _ptr(db), _ptr(work),
-                                                  nbytes, _stream(dy, stream)))
+                                                  nbytes, handle))
     return dz, dw, db
 
 
