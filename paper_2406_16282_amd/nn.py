@@ -96,6 +96,15 @@ def _weight_grad(dz, x2):
     return binding.linear_weight_grad(dz, x2) if _in_kernels(dz, x2) else dz.t().mm(x2)
 
 
+def _two_products(a, b, c, d):
+    """a b + c d. The second product is added in place (out of place the first one is copied
+    before), except under autocast, which casts no operand of an in-place call."""
+    first = a @ b
+    if torch.is_autocast_enabled(first.device.type):
+        return torch.addmm(first, c, d)
+    return first.addmm_(c, d)
+
+
 class _LinearAct(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, bias, which):
@@ -160,8 +169,7 @@ class _LinearSwiGLU(torch.autograd.Function):
     def backward(ctx, dh):
         x2, w_gate, w_up, s, u, codes = ctx.saved_tensors
         dg, du = binding.reswiglu2_bwd(_flat(dh).reshape(-1, w_gate.shape[0]), u, s, codes)
-        # the second product is added in place (out of place copies the first one before)
-        dx = (dg @ w_gate).addmm_(du, w_up).reshape(ctx.x_shape) if ctx.needs_input_grad[0] else None
+        dx = _two_products(dg, w_gate, du, w_up).reshape(ctx.x_shape) if ctx.needs_input_grad[0] else None
         dwg = _weight_grad(dg, x2) if ctx.needs_input_grad[1] else None
         dwu = _weight_grad(du, x2) if ctx.needs_input_grad[2] else None
         return dx, dwg, dwu
