@@ -556,7 +556,10 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void linear_act_fwd_rows_kernel
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][kk], fx[i][kk], acc[i][j], 0, 0, 0);
     d = d + 1 == D ? 0 : d + 1;
   }
-  __syncthreads();   // every load has landed and every ring is read: its place holds the sums
+  // The rings' place holds the sums from here on: no load may still land there (a barrier
+  // alone does not promise that), and every ring must have been read.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
   auto part = reinterpret_cast<f32x4 (*)[MT][2][kWave]>(lds);
 #pragma unroll
   for (int i = 0; i < MT; ++i)
