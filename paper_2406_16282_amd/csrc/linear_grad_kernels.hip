@@ -74,10 +74,15 @@ __device__ inline u32x4 rsrc(uint64_t base, uint32_t bytes) {
 }
 // 16 bytes per lane into LDS at `dst` + lane * 16 (see the file comment). The wait states
 // cover a resource whose registers a VALU operation has just written (5, with the move).
+// The compiler reserves m0 for itself and warns that it cannot keep a value there across
+// the asm; the clobber is to say just that, so that it never counts on one.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void load_lds16(const u32x4& r, uint32_t dst, uint32_t offset) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(dst), "v"(offset), "s"(r) : "memory");
+               :: "s"(dst), "v"(offset), "s"(r) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ inline uint32_t lds_addr(const uint16_t* p) { return uint32_t(uintptr_t((lds_void*)p)); }
 __device__ inline s16x4 read_tr(const uint16_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
