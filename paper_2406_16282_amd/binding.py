@@ -17,6 +17,7 @@ import importlib.machinery
 import importlib.util
 import math
 import os
+import warnings
 
 import torch
 
@@ -118,13 +119,15 @@ def _bind_fast(L):
     global _fast
     if _raw_stream is None:
         return   # no raw handle of the current stream: every call takes the Python path
-    if not os.path.exists(FAST_PATH):
-        raise RuntimeError(
-            f"{FAST_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
     loader = importlib.machinery.ExtensionFileLoader("_fastcall", FAST_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fastcall", loader))
-    loader.exec_module(module)
-    module.bind(_raw_stream)
+    try:   # missing, or built against another torch: the Python path does the same, slower
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fastcall", loader))
+        loader.exec_module(module)
+        module.bind(_raw_stream)
+    except (ImportError, OSError) as e:
+        warnings.warn(f"calls are marshalled in Python ({e}); build {FAST_PATH} with "
+                      "`python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=3)
+        return
     for name in (*ACT_OPS, *NORM_OPS, *GLU_OPS, "linear_act_fwd", "linear_swiglu_fwd", "msrms_linear_act_fwd",
                  "msrms_linear_swiglu_fwd"):
         _address[name] = ctypes.cast(getattr(L, name), ctypes.c_void_p).value

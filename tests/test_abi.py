@@ -219,6 +219,19 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
         B.lib()
 
 
+@pytest.mark.parametrize("content", [None, b"no library"])
+def test_binding_works_without_its_native_marshalling(monkeypatch, tmp_path, content):
+    """The Python path is complete: without the native form of the calls there is a warning."""
+    path = tmp_path / "_fastcall.so"
+    if content is not None:
+        path.write_bytes(content)
+    for name, value in (("_lib", None), ("_fast", None), ("FAST_PATH", str(path))):
+        monkeypatch.setattr(B, name, value)
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        assert B.lib().lmbp_codes_bytes(17) == 8
+    assert B._fast is None and B.codes_words(33) == 3
+
+
 def test_binding_rejects_cpu_tensors(L):
     import torch
     with pytest.raises(ValueError):
