@@ -275,11 +275,11 @@ lmbp_status msrms_linear_swiglu_fwd(lmbp_dtype dt, int64_t m, int64_t n, int64_t
  *
  *   dt  : LMBP_BF16 only. m, n, k >= 0; n a multiple of 16, k of 8; n, k <= 2^24.
  *   dz, dy [m x n], x [m x k], dw [n x k], db [n]. linear_act_bwd: codes as written by
- *         the forward; dw NULL: not computed (x is then not used); dx == dy of an
- *         activation backward is not allowed here: dz overlaps no other buffer.
+ *         the forward; dw NULL: not computed (x is then not used); db NULL: not computed;
+ *         dz overlaps no other buffer (not in place, as an activation backward may be).
  *   workspace : lmbp_linear_grad_bytes(m, n, k, bias) bytes on the calling thread's
- *         current device, 16-byte aligned (bias: nonzero for linear_act_bwd). NULL if
- *         that is 0. Its contents do not matter before or after.
+ *         current device, 16-byte aligned (bias: nonzero if db is computed; k: 0 if dw is
+ *         not). NULL if that is 0. Its contents do not matter before or after.
  * All tensors 16-byte aligned (db: 2, codes: 4); m == 0 gives zeros.
  * ------------------------------------------------------------------------ */
 size_t lmbp_linear_grad_bytes(int64_t m, int64_t n, int64_t k, int bias);

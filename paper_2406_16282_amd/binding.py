@@ -558,7 +558,7 @@ def linear_act_bwd(dy, codes, x, act="gelu", weight_grad=True, stream=None):
         raise ValueError("codes must be the int32 buffer written by the forward")
     L = lib()
     with _device_of(dy):   # launches go to the tensors' GPU
-        nbytes = L.lmbp_linear_grad_bytes(m, n, k, 1)
+        nbytes = L.lmbp_linear_grad_bytes(m, n, k if weight_grad else 0, 1)
         handle = _stream(dy, stream)
         work = _workspace(nbytes, dy, stream)
         dz = torch.empty_like(dy)

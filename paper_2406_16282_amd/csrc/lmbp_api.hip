@@ -318,7 +318,7 @@ lmbp_status linear_grad_impl(bool with_act, lmbp_act act, lmbp_dtype dt, int64_t
   for (const void* p : sixteen)
     if (p && !aligned(p, 16)) return LMBP_EINVAL;
   if ((db && !aligned(db, 2)) || (codes && !aligned(codes, 4))) return LMBP_EINVAL;
-  const uint64_t need = lmbp::linear_grad_workspace(m, n, k, db != nullptr);
+  const uint64_t need = lmbp::linear_grad_workspace(m, n, grad ? k : 0, db != nullptr);   // no dw: no partial sums
   if (need > 0 && (!workspace || workspace_bytes < 0 || uint64_t(workspace_bytes) < need)) return LMBP_EINVAL;
   const uint64_t mn = uint64_t(m) * uint64_t(n) * 2, mk = uint64_t(m) * uint64_t(k) * 2;
   const Span sdw = span(dw, grad ? uint64_t(n) * uint64_t(k) * 2 : 0);

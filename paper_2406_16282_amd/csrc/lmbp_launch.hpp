@@ -70,7 +70,7 @@ hipError_t launch_linear_rms_glu_fwd(int64_t M, int64_t N, int64_t K, float eps,
 // Backward of a fused linear layer's parameters. db non-null: dz = dy slope[code] is
 // computed here (act) and db is the column sums of dz; else dz is an input. dw non-null:
 // dw = bf16(dz^T x). Workspace of linear_grad_workspace bytes (of the same sizes; bias: db
-// non-null). N % 16 == 0, K % 8 == 0, every tensor 16-byte aligned, db 2-byte aligned.
+// non-null; K = 0 if dw is null). N % 16 == 0, K % 8 == 0, every tensor 16-byte aligned, db 2-byte aligned.
 size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias);
 hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const void* dy, const uint32_t* codes,
                               const void* x, void* dz, void* dw, void* db, void* workspace, hipStream_t s);

@@ -262,3 +262,17 @@ def test_stepact_errors(L):
     assert b(2, lv4, B.BF16, 16, x, x + 4, y, None) == B.EOVERLAP
     # words of floor(32/k) codes: 2, 3, 4 (10 per word), 5 words for 33 elements; k = 5: 0
     assert [L.lmbp_stepact_codes_bytes(k, 33) for k in (1, 2, 3, 4, 5)] == [8, 12, 16, 20, 0]
+
+
+def test_gradient_workspace(L):
+    """Partial sums are asked for only where dw is computed; the sizes without a device are
+    those of 256 CUs."""
+    m, n, k = 12608, 3072, 768
+    size = L.lmbp_linear_grad_bytes
+    sums, both = size(m, n, 0, 1), size(m, n, k, 1)
+    assert 0 < sums < both and size(m, n, k, 0) == both - sums and size(m, n, 0, 0) == 0
+    dy, c, x, dz, db, w = (P + (i << 32) for i in range(6))
+    f = lambda dw, nbytes, dz=dy: L.linear_act_bwd(0, B.BF16, m, n, k, dy, c, x, dz, dw, db, w, nbytes, None)
+    # dz on dy is refused once the workspace has been found large enough
+    assert f(None, sums) == B.EOVERLAP and f(None, sums - 1) == B.EINVAL
+    assert f(P + (7 << 32), both) == B.EOVERLAP and f(P + (7 << 32), both - 1) == B.EINVAL
