@@ -313,43 +313,57 @@ __global__ __launch_bounds__(C::kThreads, C::kMinWaves) void grad_weight_kernel(
 }
 
 // dz = dy * slope[code] as the activation kernels compute it, and the sums of the rounded dz
-// over blocks of 32 rows, per column (fp32): the read of dz that a separate sum would take
-// is saved. A wave takes 512 columns, 8 per lane, of 8 rows, all requested at once; the four
-// waves of a block add theirs in LDS. Needs 16-byte aligned tensors and N % 16 == 0.
-constexpr int kColRows = 32;
-template <int ACT>
+// over a block's rows, per column (fp32): the read of dz that a separate sum would take is
+// saved. 2^lanes_log lanes of a wave take a row's columns, 8 per lane, the others the rows
+// after it (narrow rows); a wave has ROWS such pieces requested at once, the four waves of
+// a block take consecutive ones, and a block goes on gridDim.y such groups further down. In
+// the end the lanes and waves of a column add their sums. The blocks along the columns are
+// neighbours, so that whole rows are in flight together: with those along the rows as
+// neighbours, blocks next to each other were a power of two apart for the usual widths.
+// Needs 16-byte aligned tensors and N % 16 == 0.
+template <int ACT, int ROWS>
 __global__ __launch_bounds__(256) void act_bwd_cols_kernel(const void* dy, const uint32_t* __restrict__ codes,
                                                            void* dz, float* __restrict__ sums, int64_t M,
-                                                           int64_t N) {
+                                                           int64_t N, int lanes_log) {
   using A = ActOf<ACT>;
-  constexpr int kRows = kColRows / 4;
   __shared__ float part[4][8][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_in_block();
-  const int64_t col = int64_t(blockIdx.y) * 512 + lane * 8;
-  const int64_t row0 = int64_t(blockIdx.x) * kColRows + wave * kRows;
+  const int lanes = 1 << lanes_log, piece = kWave >> lanes_log;   // rows of a piece
+  const int64_t col = int64_t(blockIdx.x) * 512 + (lane & (lanes - 1)) * 8;
   const bool in_col = col < N;
   float sum[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  u32x4 v[kRows];
-  uint32_t w[kRows];
+  const int64_t step = int64_t(gridDim.y) * (4 * ROWS * piece);
+  for (int64_t base = (int64_t(blockIdx.y) * 4 + wave) * (ROWS * piece); base < M; base += step) {
+    const int64_t row = base + (lane >> lanes_log);
+    u32x4 v[ROWS];
+    uint32_t w[ROWS];
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t at = (row0 + r) * N + col;
-    const bool in = in_col && row0 + r < M;
-    v[r] = in ? ldg16<true>(dy, at / 8) : u32x4{0u, 0u, 0u, 0u};
-    w[r] = in ? codes[at / 16] >> (16 * (lane & 1)) : 0u;
+    for (int r = 0; r < ROWS; ++r) {
+      const int64_t at = (row + r * piece) * N + col;
+      const bool in = in_col && row + r * piece < M;
+      v[r] = in ? ldg16<true>(dy, at / 8) : u32x4{0u, 0u, 0u, 0u};
+      w[r] = in ? codes[at / 16] >> (16 * (lane & 1)) : 0u;
+    }
+    float group[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      float f[8];
+      BF16::unpack(v[r], f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = f[e] * seg_slope<A>((w[r] >> (2 * e)) & 3u);
+      const u32x4 out = BF16::pack(f);
+      if (in_col && row + r * piece < M) stg16(dz, ((row + r * piece) * N + col) / 8, out);
+      BF16::unpack(out, f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) group[e] += f[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[e] += group[e];
   }
+  for (int off = lanes; off < kWave; off *= 2) {
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    float f[8];
-    BF16::unpack(v[r], f);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = f[e] * seg_slope<A>((w[r] >> (2 * e)) & 3u);
-    const u32x4 out = BF16::pack(f);
-    if (in_col && row0 + r < M) stg16(dz, ((row0 + r) * N + col) / 8, out);
-    BF16::unpack(out, f);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sum[e] += f[e];
+    for (int e = 0; e < 8; ++e) sum[e] += __shfl_xor(sum[e], off, kWave);
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) part[wave][e][lane] = sum[e];
@@ -358,14 +372,14 @@ __global__ __launch_bounds__(256) void act_bwd_cols_kernel(const void* dy, const
   for (int c = 0; c < 2; ++c) {
     const int e = threadIdx.x / kWave + 4 * c;
     const float t = ((part[0][e][lane] + part[1][e][lane]) + part[2][e][lane]) + part[3][e][lane];
-    if (in_col) sums[int64_t(blockIdx.x) * N + col + e] = t;
+    if (in_col && lane < lanes) sums[int64_t(blockIdx.y) * N + col + e] = t;
   }
 }
 
 // The second passes, in one launch. The first dw_blocks blocks: dw = bf16(sum of the
 // splits' partial sums, in split order), 8 values per thread. The others: db = bf16(sum of
 // the row blocks' column sums, in a fixed order), 16 columns per block, 16 threads to a
-// column, each with four loads in flight (one thread to a column and a quarter of the rows
+// column, each with eight loads in flight (one thread to a column and a quarter of the rows
 // was a chain of 50 loads: 23 us).
 __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ part, uint16_t* dw, int64_t n,
                                                           int splits, int64_t dw_blocks,
@@ -376,9 +390,9 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restric
     const int c = threadIdx.x % 16, q = threadIdx.x / 16;
     const int64_t col = (int64_t(blockIdx.x) - dw_blocks) * 16 + c;   // cols is a multiple of 16
     float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int64_t b = q; b < row_blocks; b += 64) {
+    for (int64_t b = q; b < row_blocks; b += 128) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) t[u] += b + 16 * u < row_blocks ? sums[(b + 16 * u) * cols + col] : 0.0f;
+      for (int u = 0; u < 8; ++u) t[u % 4] += b + 16 * u < row_blocks ? sums[(b + 16 * u) * cols + col] : 0.0f;
     }
     red[q][c] = (t[0] + t[1]) + (t[2] + t[3]);
     __syncthreads();
@@ -499,7 +513,31 @@ hipError_t launch_tile(GradArgs a, const Plan& plan, int dev, int cus, hipStream
   return hipGetLastError();
 }
 
-int64_t col_blocks(int64_t M) { return std::max<int64_t>(1, (M + kColRows - 1) / kColRows); }
+// Launch of act_bwd_cols_kernel: pieces per wave at once, lanes to a row (log2), blocks along
+// the columns and along the rows, the latter with the same number of groups each (one
+// less in the last ones). Four pieces and at most 1280 blocks (5 per CU) up to 2^27 values,
+// eight and at most 2048 beyond: 12608 x 4096 43.5 us with four, 51 with eight; 300000 x 768
+// 228 with eight, 250 with four; 1024 blocks lose up to 13% (3152 x 5632), 1792 and more up to
+// 15% (50000 x 768). Measured with the second pass, before (one block to 32 rows, any size,
+// those along the rows as neighbours) and now: 700 x 3072 11.5 and 9.4 us, 12608 x 3072 42 and
+// 35.5, 300000 x 4112 1690 and 1300 (a separate sum after the activation kernel: 1380),
+// 300000 x 16 104 and 13.4 (25); of 200 sizes four are slower, by 5 to 8% (4096 x 4000: 20.2 and
+// 21.9). The number of blocks also keeps the launch within 2^32 threads at any M.
+struct ColPlan {
+  int pieces, lanes_log;
+  int64_t columns, rows;
+};
+ColPlan col_plan(int64_t M, int64_t N) {
+  const bool large = M * N > (int64_t(1) << 27);
+  ColPlan p{large ? 8 : 4, 6, (N + 511) / 512, 1};
+  while (p.lanes_log > 1 && N <= (4 << p.lanes_log)) --p.lanes_log;
+  const int64_t group = int64_t(4 * p.pieces) << (6 - p.lanes_log);
+  const int64_t groups = std::max<int64_t>(1, (M + group - 1) / group);
+  const int64_t most = large ? 2048 : 1280;
+  const int64_t each = (groups * p.columns + most - 1) / most;
+  p.rows = (groups + each - 1) / each;
+  return p;
+}
 
 int64_t partial_floats(int64_t N, int64_t K, const Plan& p) { return p.splits > 1 ? p.splits * N * K : 0; }
 
@@ -509,7 +547,7 @@ size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias) {
   int dev = 0, cus = 256;
   if (lgrad::current_device(dev, cus) != hipSuccess) cus = 256;   // a size to plan with, no device here
   const lgrad::Plan plan = lgrad::make_plan(M, N, K, cus);
-  return size_t(lgrad::partial_floats(N, K, plan) + (bias ? lgrad::col_blocks(M) * N : 0)) * sizeof(float);
+  return size_t(lgrad::partial_floats(N, K, plan) + (bias ? lgrad::col_plan(M, N).rows * N : 0)) * sizeof(float);
 }
 
 hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const void* dy, const uint32_t* codes,
@@ -521,12 +559,12 @@ hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const vo
   const Plan plan = make_plan(M, N, K, cus);
   float* const part = static_cast<float*>(workspace);
   float* const sums = part + (dw != nullptr ? partial_floats(N, K, plan) : 0);
+  const ColPlan cols = col_plan(M, N);
   if (db != nullptr) {
-    const dim3 grid(unsigned(col_blocks(M)), unsigned((N + 511) / 512));
-    if (act == kGelu)
-      hipLaunchKernelGGL((act_bwd_cols_kernel<kGelu>), grid, dim3(256), 0, s, dy, codes, dz, sums, M, N);
-    else
-      hipLaunchKernelGGL((act_bwd_cols_kernel<kSilu>), grid, dim3(256), 0, s, dy, codes, dz, sums, M, N);
+    const auto kernel = act == kGelu ? (cols.pieces == 4 ? act_bwd_cols_kernel<kGelu, 4> : act_bwd_cols_kernel<kGelu, 8>)
+                                     : (cols.pieces == 4 ? act_bwd_cols_kernel<kSilu, 4> : act_bwd_cols_kernel<kSilu, 8>);
+    hipLaunchKernelGGL(kernel, dim3(unsigned(cols.columns), unsigned(cols.rows)), dim3(256), 0, s, dy, codes, dz, sums,
+                       M, N, cols.lanes_log);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -549,7 +587,7 @@ hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const vo
   if (dw_blocks + db_blocks > 0) {
     hipLaunchKernelGGL(grad_reduce_kernel, dim3(unsigned(dw_blocks + db_blocks)), dim3(256), 0, s, part,
                        static_cast<uint16_t*>(dw), N * K, int(plan.splits), dw_blocks, sums,
-                       static_cast<uint16_t*>(db), N, col_blocks(M));
+                       static_cast<uint16_t*>(db), N, cols.rows);
     e = hipGetLastError();
   }
   return e;

@@ -75,7 +75,7 @@ def test_resilu2_beyond_int32(offset):
 @pytest.mark.parametrize("op,cols", [("msrms", 4096), ("msln", 4100)])
 def test_norm_beyond_int32(op, cols):
     """msrms with 4096-wide rows: register-tile path; msln with 4100-wide bf16 rows (not
-    16-byte multiples): block-per-row path. Chained check: each side runs its own
+    16-byte multiples): the same path with rows that start at any element. Chained check: each side runs its own
     forward, then its backward."""
     rows = (1 << 31) // cols + 5
     n = rows * cols
@@ -103,3 +103,25 @@ def test_norm_beyond_int32(op, cols):
     assert_mixed(oracle.decode(H(z[st]), "bf16"), z_o, 1e-2, f"{op} z beyond 2^31")
     assert_rel(H(rstd[st]).astype(np.float64), r_o, 1e-5, f"{op} rstd beyond 2^31", floor=0.0)
     assert_mixed(oracle.decode(H(dx[st]), "bf16"), dx_o, 1e-2, f"{op} dx beyond 2^31 (chained)")
+
+
+def test_bias_gradient_beyond_2_29_rows():
+    """More 32-row groups than one block each could take within a launch of 2^32 threads. The
+    sums are compared over parts of the rows in float64: the fp32 sums of the kernel are
+    within 2^-8 of the value (the rounding to bf16) and, for sums kept in several hundred
+    partial ones, 2^-12 of the absolute sum."""
+    m, n, part = (1 << 29) + 5, 16, 1 << 25
+    print(f"[large] bias gradient {m} x {n}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(0)
+    dy = torch.empty((m, n), device=DEV, dtype=torch.bfloat16).normal_(0.01, 1.0, generator=g)
+    codes = torch.empty(m, device=DEV, dtype=torch.int32).random_(generator=g)
+    dz, _, db = lmbp.linear_act_bwd(dy, codes, torch.empty((m, 8), device=DEV, dtype=torch.bfloat16), "gelu",
+                                    weight_grad=False)
+    exact, size = torch.zeros((2, n), device=DEV, dtype=torch.float64)
+    for a in range(0, m, part):
+        ref = lmbp.regelu2_bwd(dy[a:a + part], codes[a:a + part])
+        assert torch.equal(dz[a:a + part].view(torch.int16), ref.view(torch.int16)), f"rows from {a}"
+        exact += ref.sum(0, dtype=torch.float64)
+        size += ref.abs().sum(0, dtype=torch.float64)
+    assert ((db.double() - exact).abs() <= exact.abs() * 2.0 ** -8 + size * 2.0 ** -12).all()

@@ -57,6 +57,27 @@ def test_act_bwd_with_bias(m, n, k, act):
     assert none is None and torch.equal(dz2, dz) and torch.equal(db2, db)
 
 
+@pytest.mark.parametrize("m,n", [
+    (1, 16), (511, 16), (513, 16), (5, 32), (257, 48), (1025, 64), (129, 128), (70001, 144), (33, 256), (20011, 272),
+    (100001, 512), (4099, 1040), (3001, 4112),       # lanes to a row 2 .. 64, one and several groups to a block
+    (600011, 240), (33001, 4112), (9001, 16400),     # eight pieces at once
+    (1, 1 << 20)])                                   # more blocks along the columns than are wanted in all
+def test_bias_gradient_pieces(m, n):
+    """dz and db without dw; bounds as above."""
+    print(f"[grad] db {m} {n}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m + n)
+    dy = torch.randn((m, n), generator=g, device=DEV, dtype=torch.bfloat16)
+    codes = torch.randint(-2 ** 31, 2 ** 31, (m * n // 16,), generator=g, device=DEV, dtype=torch.int32)
+    dz, _, db = lmbp.linear_act_bwd(dy, codes, torch.empty((m, 8), device=DEV, dtype=torch.bfloat16), "silu",
+                                    weight_grad=False)
+    assert torch.equal(dz.view(torch.int16), lmbp.resilu2_bwd(dy, codes).view(torch.int16))
+    exact, size = dz.sum(0, dtype=torch.float64), dz.abs().sum(0, dtype=torch.float64)
+    assert ((db.double() - exact).abs() <= exact.abs() * 2.0 ** -8 + size * m * 2.0 ** -24 * 1.01).all()
+    db2 = lmbp.linear_act_bwd(dy, codes, torch.empty((m, 8), device=DEV, dtype=torch.bfloat16), "silu")[2]
+    assert torch.equal(db, db2)   # the same sums in the same order
+
+
 @pytest.mark.parametrize("needs", [(True, True, True), (False, True, True), (True, False, True), (True, True, False)])
 def test_module_gradients_against_recorded_backward(needs):
     """The kernels' gradients against those of a recorded backward (create_graph), which
