@@ -71,6 +71,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 namespace lmbp {
 namespace lin {
@@ -677,59 +678,103 @@ hipError_t launch_tile(LinArgs a, int dev, int cus, hipStream_t s) {
 }
 
 // Estimated time of a tile configuration, in us: full rounds of the resident blocks and a
-// partial one, in which a CU with fewer blocks is faster. The coefficients are
-// least-squares fits (relative error 7 to 12% rms) to the measured times of each
-// configuration on 256 CUs: kLinearCost on M = 16 .. 12608 rows of layers from K x N =
-// 512 x 2048 to 1024 x 4096 with GELU and three gated ones, kGatedCost on M = 16 .. 4096
-// rows of six gated layers from 520 x 4112 to 5120 x 13824. The gated form has terms of
-// its own because its epilogue writes three tensors and the codes: a round of 64 x 128
-// tiles costs 9 us there beside its K steps, not 2. Its fit weighs a time by how near it is
-// to the layer's fastest, and that round is 3 us and the 128 x 256 one -1 us from its
-// least-squares value, in the middle of the range that gives the same choices. The choice
-// is 1.1% slower than the fastest configuration on average (one set of terms for both
-// forms: 2.6%, and 57 us where 46 were to be had at 2000 rows of 520 x 4112). The single
-// rule used before (256 x 256 tiles from four rounds of them on, else 128 x 128) was 18%
-// slower on average: 1024 rows of the 4096 x 11008 gated layer 213 us against 181, 2048
-// rows 416 against 302.
+// partial one, in which a CU with one block (or two of three) is faster, the more so the fewer
+// CUs have it; K steps that are longer where rows do not begin on 128-byte lines; the
+// bytes of W, x and the outputs. The coefficients are non-negative least-squares fits of the
+// relative error (one set per configuration, plain and gated) to the times on 256 CUs of
+// M = 1 .. 16384 rows of 13 layers from 256 x 256 to 8192 x 1024 and 640 x 5120 with GELU, and of
+// M = 1 .. 4096 rows of 11 gated ones from 1024 x 1024 to 14336 x 4096: 377 and 308 sizes, inputs
+// and weights not in the caches, those near the size's best weighing more. The choice is 0.3%
+// (gated 0.4%) slower than the fastest form on average, 8% (10%) at worst; with each layer's choices
+// made by a fit to the other layers, 0.6% (0.8%), 21% (18%). A fit to fewer layers with fewer
+// terms was 4.3% (2.2%) slower on average, 48% (24%) at worst: 4096 rows of 256 x 256 10.1 us
+// against 7.7, 2500 of 4096 x 1024 41 against 32, 1500 of the gated 3072 x 768 34 against 26.
 struct Cost {
-  float base, step_full, step_any, step_second, step_third, step_load, full, any, second;
+  float base, step_full, step_any, step_second, step_third, step_load, full, any, second, w_mb, out_mb, x_mb, w_full_mb,
+      step_ragged, load_second, load_third, load_first;
 };
 template <class C, bool GLU>
 float cost(const LinArgs& a, int cus, const Cost& c) {
   const int64_t tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + kOutCols<C, GLU> - 1) / kOutCols<C, GLU>);
-  const int64_t slots = int64_t(cus) * C::kBlocksPerCu;
-  const int64_t full = tiles / slots, rest = tiles % slots;
-  const float any = rest > 0, second = rest > cus, third = rest > 2 * int64_t(cus);
-  const float per_step = c.step_full * float(full) + c.step_any * any + c.step_second * second +
-                         c.step_third * third + c.step_load * (float(rest) / float(slots));
-  return c.base + float((a.K + kBK - 1) / kBK) * per_step + c.full * float(full) + c.any * any + c.second * second;
+  const int64_t slots = int64_t(cus) * C::kBlocksPerCu, rest = tiles % slots;
+  const float full = float(tiles / slots), any = rest > 0, second = rest > cus, third = rest > 2 * int64_t(cus);
+  const float load = float(rest) / float(slots), ragged = a.K % 64 != 0;
+  const float per_cu = float(rest) / float(cus);   // blocks of the partial round on a CU
+  const float level = third > 0.0f    ? c.load_third * (per_cu - 2.0f)
+                      : second > 0.0f ? c.load_second * (per_cu - 1.0f)
+                                      : c.load_first * per_cu;
+  const float w_mb = float(a.N) * float(a.K) * (GLU ? 4e-6f : 2e-6f);
+  const float per_step = c.step_full * full + c.step_any * any + c.step_second * second + c.step_third * third +
+                         c.step_load * load + level + c.step_ragged * ragged * (full + load);
+  return c.base + float((a.K + kBK - 1) / kBK) * per_step + c.full * full + c.any * any + c.second * second +
+         (c.w_mb + c.w_full_mb * full) * w_mb + c.out_mb * float(a.M) * float(a.N) * (GLU ? 6e-6f : 2e-6f) +
+         c.x_mb * float(a.M) * float(a.K) * 2e-6f;
 }
 struct TileCosts {
   Cost big, mid, small, low;
 };
-constexpr TileCosts kLinearCost = {{5.53f, 1.386f, 0.844f, 0.0f, 0.0f, 0.735f, 17.28f, 10.29f, 0.0f},
-                                   {10.13f, 1.567f, 0.739f, 0.241f, 0.0f, 0.901f, 14.30f, 0.33f, 5.46f},
-                                   {4.51f, 1.027f, 0.468f, 0.257f, 0.0f, 0.569f, 6.06f, 0.21f, 0.96f},
-                                   {2.87f, 1.091f, 0.484f, 0.177f, 0.164f, 0.447f, 2.32f, 0.0f, 0.0f}};
-constexpr TileCosts kGatedCost = {{1.39f, 1.311f, 0.833f, 0.0f, 0.0f, 0.789f, 19.35f, 13.27f, 0.0f},
-                                  {0.0f, 1.366f, 0.842f, 0.149f, 0.0f, 0.831f, 21.57f, 6.72f, 8.18f},
-                                  {0.0f, 0.863f, 0.471f, 0.171f, 0.0f, 0.689f, 10.82f, 3.93f, 1.20f},
-                                  {1.20f, 0.963f, 0.601f, 0.125f, 0.302f, 0.271f, 8.88f, 0.0f, 1.46f}};
+constexpr TileCosts kLinearCost = {
+    {5.921f, 1.526f, 1.015f, 0, 0, 0.3973f, 7.993f, 7.732f, 0, 0, 0.1274f, 0.04803f, 0, 0.03257f, 0, 0, 0},
+    {8.992f, 1.649f, 0.6745f, 0.5608f, 0, 0, 4.083f, 1.508f, 1.367f, 0, 0.1426f, 0.03935f, 0.003606f, 0.2174f,
+     0.3989f, 0, 0.1587f},
+    {4.783f, 0.9873f, 0.4192f, 0.3014f, 0, 0, 1.069f, 0.549f, 0.878f, 0.005972f, 0.2383f, 0.0543f, 0, 0.2342f,
+     0.2733f, 0, 0.1053f},
+    {4.617f, 0.9295f, 0.3228f, 0.149f, 0.3207f, 0, 0.8561f, 0, 0.4019f, 0.008148f, 0.1836f, 0.07334f, 0, 0.3088f,
+     0.1102f, 0.1466f, 0.03835f}};
+constexpr TileCosts kGatedCost = {
+    {5.759f, 1.485f, 0.955f, 0, 0, 0.6037f, 7.985f, 4.71f, 0, 0, 0.07038f, 0, 0, 0, 0, 0, 0},
+    {7.16f, 1.561f, 0.7105f, 0.4801f, 0, 0, 6.558f, 0.4042f, 1.888f, 0.06568f, 0.08794f, 0, 0, 0.0264f, 0.598f, 0,
+     0.1684f},
+    {4.17f, 0.8531f, 0.4276f, 0.3526f, 0, 0, 0.8689f, 0, 0, 0.07132f, 0.2383f, 0, 0.03413f, 0.04145f, 0.1557f, 0,
+     0.0532f},
+    {3.449f, 0.9078f, 0.3368f, 0.1544f, 0.332f, 0, 0.02381f, 0.08592f, 0, 0.1044f, 0.1717f, 0, 0.03171f, 0.2471f,
+     0.1276f, 0.08594f, 0}};
 
-// The same for the split-K form, fitted to 16 .. 512 rows of the same layers: a latency,
-// the chain of a wave's K steps, and the bytes that all blocks take in (per MB, 256 CUs).
-// With it 0.7% over the fastest form on average.
+// The same for the split-K form (in the same fit): a latency, the chain of a wave's K steps,
+// longer from 1 .. 5 blocks on a CU on (`chain_more`) and with every 4 more, the bytes that all
+// blocks take in, and those of W, x and the outputs.
 struct RowsCost {
-  float base, step, mb;
+  float base, chain, mb, blocks, w_mb, out_mb, ragged_mb, chain_more[5], chain_round, round, x_mb;
 };
-constexpr RowsCost kRows16Cost = {1.59f, 0.542f, 0.0578f}, kRows32Cost = {2.21f, 0.401f, 0.0625f};
+struct RowsCosts {
+  RowsCost rows16, rows32;
+};
+constexpr RowsCosts kLinearRowsCost = {
+    {2.721f, 0.1513f, 0.01166f, 1.058f, 0, 0.7846f, 0.004431f, {0.1165f, 0.1443f, 0.1586f, 0, 0.2964f}, 0.233f,
+     0.9253f, 0.8186f},
+    {2.92f, 0.2037f, 0.00706f, 1.167f, 0, 0.5465f, 0.003384f, {0.1687f, 0.4693f, 0.1883f, 0, 0.5173f}, 0.4701f,
+     1.493f, 0.9763f}};
+constexpr RowsCosts kGatedRowsCost = {
+    {2.568f, 0.1036f, 0.0152f, 0.749f, 0.1047f, 0.3545f, 0, {0.1776f, 0.1262f, 0.124f, 0, 0.1921f}, 0.387f,
+     0.1411f, 0},
+    {2.686f, 0.1603f, 0.006446f, 0, 0.1014f, 1.025f, 0.0008366f, {0.2669f, 0.2736f, 0.1568f, 0, 0.2646f}, 0.5871f,
+     0, 0}};
 template <int MT, bool GLU>
 float rows_cost(const LinArgs& a, int cus, const RowsCost& c) {
   constexpr int kOut = GLU ? 16 : 32;
   const float blocks = float((a.M + MT * 16 - 1) / (MT * 16)) * float((a.N + kOut - 1) / kOut);
-  const float steps = float((a.K + kBK - 1) / kBK);
-  return c.base + c.step * steps / kRowsWaves +
-         c.mb * blocks * steps * float((32 + MT * 16) * kBK * 2) * 1e-6f * 256.0f / float(cus);
+  const int64_t steps = (a.K + kBK - 1) / kBK;
+  const float per_cu = blocks / float(cus);
+  float chain = c.chain;
+  for (int i = 0; i < 5; ++i) chain += per_cu > float(i + 1) ? c.chain_more[i] : 0.0f;
+  const float rounds = std::max(0.0f, std::ceil(per_cu / 4.0f) - 1.0f);
+  const float mb = blocks * float(steps) * float((32 + MT * 16) * kBK * 2) * 1e-6f * 256.0f / float(cus);
+  return c.base + (chain + c.chain_round * rounds) * float((steps + kRowsWaves - 1) / kRowsWaves) + c.round * rounds +
+         (c.mb + c.ragged_mb * float(a.K % 64 != 0)) * mb + c.blocks * per_cu * 0.25f +
+         c.w_mb * float(a.N) * float(a.K) * (GLU ? 4e-6f : 2e-6f) +
+         c.out_mb * float(a.M) * float(a.N) * (GLU ? 6e-6f : 2e-6f) + c.x_mb * float(a.M) * float(a.K) * 2e-6f;
+}
+
+// The form that a layer runs in: the fastest by the estimates above.
+enum Form { kRows16, kRows32, kBig, kMid, kSmall, kLow, kForms };
+template <bool GLU>
+Form choose_form(const LinArgs& a, int cus) {
+  constexpr TileCosts c = GLU ? kGatedCost : kLinearCost;
+  constexpr RowsCosts r = GLU ? kGatedRowsCost : kLinearRowsCost;
+  const float t[kForms] = {rows_cost<1, GLU>(a, cus, r.rows16), rows_cost<2, GLU>(a, cus, r.rows32),
+                           cost<BigTile, GLU>(a, cus, c.big),   cost<MidTile, GLU>(a, cus, c.mid),
+                           cost<SmallTile, GLU>(a, cus, c.small), cost<LowTile, GLU>(a, cus, c.low)};
+  return Form(std::min_element(t, t + kForms) - t);
 }
 
 template <int MT, int ACT, bool GLU, bool NORM>
@@ -752,17 +797,14 @@ hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
   int dev = 0, cus = 0;
   const hipError_t e = current_device(dev, cus);
   if (e != hipSuccess) return e;
-  constexpr TileCosts c = GLU ? kGatedCost : kLinearCost;
-  const float big = cost<BigTile, GLU>(a, cus, c.big), mid = cost<MidTile, GLU>(a, cus, c.mid);
-  const float small = cost<SmallTile, GLU>(a, cus, c.small), low = cost<LowTile, GLU>(a, cus, c.low);
-  const float rows16 = rows_cost<1, GLU>(a, cus, kRows16Cost), rows32 = rows_cost<2, GLU>(a, cus, kRows32Cost);
-  const float tiled = std::min(std::min(big, mid), std::min(small, low));
-  if (rows16 < tiled && rows16 <= rows32) return launch_rows<1, ACT, GLU, NORM>(a, s);
-  if (rows32 < tiled) return launch_rows<2, ACT, GLU, NORM>(a, s);
-  if (big <= mid && big <= small && big <= low) return launch_tile<BigTile, ACT, GLU, NORM>(a, dev, cus, s);
-  if (mid <= small && mid <= low) return launch_tile<MidTile, ACT, GLU, NORM>(a, dev, cus, s);
-  if (small <= low) return launch_tile<SmallTile, ACT, GLU, NORM>(a, dev, cus, s);
-  return launch_tile<LowTile, ACT, GLU, NORM>(a, dev, cus, s);
+  switch (choose_form<GLU>(a, cus)) {
+    case kRows16: return launch_rows<1, ACT, GLU, NORM>(a, s);
+    case kRows32: return launch_rows<2, ACT, GLU, NORM>(a, s);
+    case kBig: return launch_tile<BigTile, ACT, GLU, NORM>(a, dev, cus, s);
+    case kMid: return launch_tile<MidTile, ACT, GLU, NORM>(a, dev, cus, s);
+    case kSmall: return launch_tile<SmallTile, ACT, GLU, NORM>(a, dev, cus, s);
+    default: return launch_tile<LowTile, ACT, GLU, NORM>(a, dev, cus, s);
+  }
 }
 
 }  // namespace lin
