@@ -292,6 +292,18 @@ lmbp_status linear_act_bwd(lmbp_act act, lmbp_dtype dt, int64_t m, int64_t n, in
                            void *stream);
 
 /* ------------------------------------------------------------------------
+ * Test utilities (host only, no launch): the kernel form that a size takes on the calling
+ * thread's current device, or on 256 CUs where there is none.
+ *   lmbp_linear_form : 0, 1 split-K with 16, 32 rows to a block; 2 .. 5 tiles of 256 x 256,
+ *                      128 x 256, 128 x 128, 64 x 128; *rounds (or NULL): the most tiles
+ *                      that one block computes. -1 for sizes that run nothing.
+ *   lmbp_linear_grad_form : 0 .. 2 tiles of 256 x 256, 128 x 256, 128 x 128; *splits (or
+ *                      NULL): the shares of the rows; *rounds (or NULL): as above.
+ * ------------------------------------------------------------------------ */
+int lmbp_linear_form(int64_t m, int64_t n, int64_t k, int gated, int64_t *rounds);
+int lmbp_linear_grad_form(int64_t m, int64_t n, int64_t k, int64_t *splits, int64_t *rounds);
+
+/* ------------------------------------------------------------------------
  * Measurement utility (not part of the method): copies `bytes` bytes from src
  * to dst with 16-byte non-temporal vector loads and non-temporal device-scope vector
  * stores (written through the L2), the fastest plain copy measured on the GPU for

@@ -99,6 +99,11 @@ def lib():
     L.msrms_linear_swiglu_fwd.restype = i32
     L.lmbp_linear_grad_bytes.argtypes = [i64, i64, i64, i32]
     L.lmbp_linear_grad_bytes.restype = ctypes.c_size_t
+    counts = ctypes.POINTER(i64)
+    L.lmbp_linear_form.argtypes = [i64, i64, i64, i32, counts]
+    L.lmbp_linear_form.restype = i32
+    L.lmbp_linear_grad_form.argtypes = [i64, i64, i64, counts, counts]
+    L.lmbp_linear_grad_form.restype = i32
     L.linear_weight_grad.argtypes = [i32, i64, i64, i64, vp, vp, vp, vp, i64, vp]
     L.linear_weight_grad.restype = i32
     L.linear_act_bwd.argtypes = [i32, i32, i64, i64, i64, vp, vp, vp, vp, vp, vp, vp, i64, vp]

@@ -550,6 +550,20 @@ size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias) {
   return size_t(lgrad::partial_floats(N, K, plan) + (bias ? lgrad::col_plan(M, N).rows * N : 0)) * sizeof(float);
 }
 
+LinearGradForm linear_grad_form(int64_t M, int64_t N, int64_t K) {
+  int dev = 0, cus = 256;
+  if (lgrad::current_device(dev, cus) != hipSuccess) cus = 256;   // no device here
+  const lgrad::Plan plan = lgrad::make_plan(M, N, K, cus);
+  auto rounds = [&](auto tile) {
+    using C = decltype(tile);
+    const int64_t units = ((N + C::BM - 1) / C::BM) * ((K + C::BN - 1) / C::BN) * plan.splits;
+    const int64_t slots = int64_t(cus) * C::kBlocksPerCu;
+    return (units + slots - 1) / slots;
+  };
+  return {plan.tile, plan.splits, plan.tile == 0 ? rounds(lgrad::BigTile{}) : plan.tile == 1 ? rounds(lgrad::MidTile{})
+                                                                                             : rounds(lgrad::SmallTile{})};
+}
+
 hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const void* dy, const uint32_t* codes,
                               const void* x, void* dz, void* dw, void* db, void* workspace, hipStream_t s) {
   using namespace lgrad;

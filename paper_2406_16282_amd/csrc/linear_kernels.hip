@@ -809,6 +809,29 @@ hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
 
 }  // namespace lin
 
+LinearForm linear_form(bool gated, int64_t M, int64_t N, int64_t K) {
+  int dev = 0, cus = 256;
+  if (lin::current_device(dev, cus) != hipSuccess) cus = 256;   // no device here
+  lin::LinArgs a{};
+  a.M = M;
+  a.N = N;
+  a.K = K;
+  const lin::Form f = gated ? lin::choose_form<true>(a, cus) : lin::choose_form<false>(a, cus);
+  auto of = [&](auto tile) -> LinearForm {
+    using C = decltype(tile);
+    const int64_t cols = gated ? C::BN / 2 : C::BN;
+    const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + cols - 1) / cols), slots = int64_t(cus) * C::kBlocksPerCu;
+    return {int(f), (tiles + slots - 1) / slots};
+  };
+  switch (f) {
+    case lin::kBig: return of(lin::BigTile{});
+    case lin::kMid: return of(lin::MidTile{});
+    case lin::kSmall: return of(lin::SmallTile{});
+    case lin::kLow: return of(lin::LowTile{});
+    default: return {int(f), 1};
+  }
+}
+
 hipError_t launch_linear_act_fwd(int act, int64_t M, int64_t N, int64_t K, const void* x,
                                  const void* w, const void* bias, void* y, uint32_t* codes,
                                  void* z, hipStream_t s) {

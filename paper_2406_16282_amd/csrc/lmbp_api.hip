@@ -476,6 +476,19 @@ lmbp_status reswiglu2_bwd(lmbp_dtype dt, int64_t n, const void* dh, const void* 
   return glu_bwd(dt, n, dh, u, s, codes, dg, du, stream);
 }
 
+int lmbp_linear_form(int64_t m, int64_t n, int64_t k, int gated, int64_t* rounds) {
+  if (m <= 0 || n <= 0 || k < 0) return -1;
+  const lmbp::LinearForm f = lmbp::linear_form(gated != 0, m, n, k);
+  if (rounds) *rounds = f.rounds;
+  return f.form;
+}
+int lmbp_linear_grad_form(int64_t m, int64_t n, int64_t k, int64_t* splits, int64_t* rounds) {
+  if (m < 0 || n <= 0 || k <= 0) return -1;
+  const lmbp::LinearGradForm f = lmbp::linear_grad_form(m, n, k);
+  if (splits) *splits = f.splits;
+  if (rounds) *rounds = f.rounds;
+  return f.tile;
+}
 size_t lmbp_linear_grad_bytes(int64_t m, int64_t n, int64_t k, int bias) {
   if (m < 0 || n <= 0 || k < 0 || n > (int64_t(1) << 24) || k > (int64_t(1) << 24)) return 0;
   return lmbp::linear_grad_workspace(m, n, k, bias != 0);

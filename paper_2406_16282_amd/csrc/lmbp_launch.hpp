@@ -67,11 +67,27 @@ hipError_t launch_linear_rms_glu_fwd(int64_t M, int64_t N, int64_t K, float eps,
                                      void* u, uint32_t* codes, void* g, void* z_norm, float* rstd,
                                      hipStream_t s);
 
+// The form that the fused forward of a layer runs in on the current device (256 CUs without
+// one): 0, 1 split-K with 16, 32 rows; 2 .. 5 tiles of 256 x 256, 128 x 256, 128 x 128, 64 x
+// 128; and the most tiles that a block computes.
+struct LinearForm {
+  int form;
+  int64_t rounds;
+};
+LinearForm linear_form(bool gated, int64_t M, int64_t N, int64_t K);
+
 // Backward of a fused linear layer's parameters. db non-null: dz = dy slope[code] is
 // computed here (act) and db is the column sums of dz; else dz is an input. dw non-null:
 // dw = bf16(dz^T x). Workspace of linear_grad_workspace bytes (of the same sizes; bias: db
 // non-null; K = 0 if dw is null). N % 16 == 0, K % 8 == 0, every tensor 16-byte aligned, db 2-byte aligned.
 size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias);
+// The tile of dW (0 .. 2: 256 x 256, 128 x 256, 128 x 128), the shares that its rows are split
+// into, and the most units of work that a block takes.
+struct LinearGradForm {
+  int tile;
+  int64_t splits, rounds;
+};
+LinearGradForm linear_grad_form(int64_t M, int64_t N, int64_t K);
 hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const void* dy, const uint32_t* codes,
                               const void* x, void* dz, void* dw, void* db, void* workspace, hipStream_t s);
 
