@@ -276,3 +276,48 @@ def test_gradient_workspace(L):
     # dz on dy is refused once the workspace has been found large enough
     assert f(None, sums) == B.EOVERLAP and f(None, sums - 1) == B.EINVAL
     assert f(P + (7 << 32), both) == B.EOVERLAP and f(P + (7 << 32), both - 1) == B.EINVAL
+
+
+def test_gradient_errors(L):
+    gap = 1 << 32
+    dz, x, dw, w, dy, c, db = (P + i * gap for i in range(7))
+    m, n, k = 700, 272, 136   # rows split: needs a workspace
+    size = L.lmbp_linear_grad_bytes
+    need = size(m, n, k, 0)
+    assert need > 0 and size(-1, n, k, 0) == size(m, 0, k, 0) == size(m, n, -8, 0) == size(m, (1 << 24) + 16, k, 0) == 0
+
+    def f(dt=B.BF16, m=m, n=n, k=k, dz=dz, x=x, dw=dw, w=w, nbytes=need):
+        return L.linear_weight_grad(dt, m, n, k, dz, x, dw, w, nbytes, None)
+
+    for dt in (B.FP32, 7):
+        assert f(dt=dt) == B.EDTYPE
+    for bad in (dict(m=-1), dict(n=-16), dict(k=-8), dict(n=264), dict(k=132), dict(m=1 << 31), dict(n=(1 << 24) + 16),
+                dict(k=(1 << 24) + 8), dict(dz=None), dict(x=None), dict(dw=None), dict(w=None), dict(nbytes=need - 1),
+                dict(nbytes=-1), dict(dz=dz + 8), dict(x=x + 2), dict(dw=dw + 4), dict(w=w + 8)):
+        assert f(**bad) == B.EINVAL, bad
+    assert f(n=0) == f(n=0, dz=None, x=None, dw=None, w=None) == B.OK   # nothing to do
+    for bad in (dict(dw=dz + 16), dict(dw=x + m * k * 2 - 16), dict(w=dw), dict(w=dz + 4096), dict(w=x), dict(dw=w + need - 16)):
+        assert f(**bad) == B.EOVERLAP, bad
+
+    need = size(m, n, k, 1)
+
+    def g(act=0, dt=B.BF16, m=m, n=n, k=k, dy=dy, c=c, x=x, dz=dz, dw=dw, db=db, w=w, nbytes=need):
+        return L.linear_act_bwd(act, dt, m, n, k, dy, c, x, dz, dw, db, w, nbytes, None)
+
+    assert g(dt=B.FP32) == B.EDTYPE and g(act=2) == B.EINVAL
+    for bad in (dict(dy=None), dict(c=None), dict(dz=None), dict(x=None), dict(w=None), dict(nbytes=need - 1), dict(c=c + 2),
+                dict(db=db + 1), dict(dy=dy + 8), dict(dz=dz + 8), dict(n=264), dict(k=132)):
+        assert g(**bad) == B.EINVAL, bad
+    for bad in (dict(dz=dy), dict(dz=x), dict(dz=c), dict(dw=dz), dict(dw=dy + 16), dict(db=dz + 2), dict(db=dw), dict(db=c),
+                dict(w=dy), dict(w=dz), dict(w=c + 16), dict(db=w + 16), dict(dw=x)):
+        assert g(**bad) == B.EOVERLAP, bad
+    # without dw, x is not used; without db, neither is its part of the workspace
+    assert g(dw=None, x=None, nbytes=size(m, n, 0, 1), dz=dy) == B.EOVERLAP
+    assert g(db=None, nbytes=size(m, n, k, 0), dz=dy) == B.EOVERLAP
+    assert g(db=None, dw=None, x=None, w=None, nbytes=0, dz=dy) == B.EOVERLAP
+    assert g(n=0, dy=None, c=None, x=None, dz=None, dw=None, db=None, w=None, nbytes=0) == B.OK
+
+
+def test_form_queries(L):
+    assert L.lmbp_linear_form(0, 16, 8, 0, None) == L.lmbp_linear_form(16, 0, 8, 1, None) == -1
+    assert L.lmbp_linear_grad_form(5, 16, 0, None, None) == -1 and L.lmbp_linear_grad_form(0, 16, 8, None, None) >= 0

@@ -178,6 +178,44 @@ def test_linear_guards():
         check_guards(rb, m, 0, f"norm swiglu linear rstd {m}x{n}x{k}")
 
 
+# rows split and whole, ragged in every dimension
+GRAD_SHAPES = [(1, 16, 8), (65, 400, 136), (700, 272, 136), (1999, 528, 520), (1375, 8176, 8)]
+
+
+@pytest.mark.parametrize("form", ["weight", "all", "bias", "dz and weight", "dz"])
+def test_gradient_guards(form):
+    """dz, dw, db and a workspace of exactly the size asked for, through the C entry points."""
+    L = binding.lib()
+    stream = torch.cuda.current_stream().cuda_stream
+    for m, n, k in GRAD_SHAPES:
+        x, dy = rnd(m * k, torch.bfloat16), rnd(m * n, torch.bfloat16)
+        codes = lmbp.resilu2_fwd(rnd(m * n, torch.bfloat16))[1]
+        with_w, with_b = form in ("weight", "all", "dz and weight"), form in ("all", "bias")
+        words = L.lmbp_linear_grad_bytes(m, n, k if with_w else 0, int(with_b)) // 4
+        bufs = {"dz": guarded(m * n, torch.bfloat16), "dw": guarded(n * k, torch.bfloat16),
+                "db": guarded(n, torch.bfloat16), "workspace": guarded(words, torch.float32)}
+        p = {name: b[1].data_ptr() for name, b in bufs.items()}
+        work = p["workspace"] if words else None
+        if form == "weight":
+            st = L.linear_weight_grad(binding.BF16, m, n, k, dy.data_ptr(), x.data_ptr(), p["dw"], work, 4 * words, stream)
+        else:
+            st = L.linear_act_bwd(binding.ACT_SILU, binding.BF16, m, n, k, dy.data_ptr(), codes.data_ptr(),
+                                  x.data_ptr() if with_w else None, p["dz"], p["dw"] if with_w else None,
+                                  p["db"] if with_b else None, work, 4 * words, stream)
+        assert st == binding.OK
+        for name, (buf, view) in bufs.items():
+            check_guards(buf, view.numel(), 0, f"gradient {form} {name} {m}x{n}x{k}")
+        # what is there is what the binding's calls give
+        ref = lmbp.resilu2_bwd(dy, codes)
+        if form == "weight":
+            assert torch.equal(bufs["dw"][1].view(n, k), lmbp.linear_weight_grad(dy.view(m, n), x.view(m, k)))
+        else:
+            assert torch.equal(bufs["dz"][1].view(torch.int16), ref.view(torch.int16))
+            _, dw, db = lmbp.linear_act_bwd(dy.view(m, n), codes, x.view(m, k), "silu")
+            assert not with_w or torch.equal(bufs["dw"][1].view(n, k), dw)
+            assert not with_b or torch.equal(bufs["db"][1], db)
+
+
 def test_copy_guards():
     for nbytes in (16, 4096 + 5, 1 << 20):
         src = torch.randint(0, 255, (nbytes,), dtype=torch.uint8, device=DEV)

@@ -96,3 +96,34 @@ def test_graph_replay_matches_eager(dtype):
                 f"replay {replay}: {k} differs from the eager result"
         _step(t, eager)               # eager work between replays
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("m,n,k", [(700, 272, 136), (197, 3072, 768), (40003, 64, 16)])
+def test_gradients_under_capture(m, n, k):
+    """The parameter gradients in a graph (the workspace comes from the graph's own memory):
+    every replay against the eager result, with new inputs, eager work and synchronisations
+    between the replays."""
+    print(f"[graph] gradients {m} {n} {k}", flush=True)
+    dy, x = (torch.randn(s, device=DEV, dtype=torch.bfloat16) for s in ((m, n), (m, k)))
+    codes = lmbp.regelu2_fwd(dy)[1]
+
+    def call():
+        return (lmbp.linear_weight_grad(dy, x), *lmbp.linear_act_bwd(dy, codes, x),
+                lmbp.linear_act_bwd(dy, codes, x, weight_grad=False)[2])
+
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = call()
+    for replay in range(3):
+        dy.normal_()
+        x.normal_()
+        for o in out:
+            o.view(torch.uint8).fill_(0xA5)
+        ref = call()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for i, (a, r) in enumerate(zip(out, ref)):
+            assert torch.equal(a.view(torch.uint8), r.view(torch.uint8)), f"replay {replay}: output {i}"
