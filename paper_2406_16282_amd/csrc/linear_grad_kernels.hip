@@ -26,9 +26,9 @@
 // A unit is a tile of dW over a share of the rows: small dW are split over the rows to fill
 // the device, the shares' fp32 sums go to a workspace and are added in order by a second
 // kernel. What bounds it: for large dW the card's power, as the forward; for split ones
-// the partial sums' traffic besides. Measured against the library's product: 8192 rows of
-// 11008 x 4096 581 against 785 us, 12608 of 3072 x 768 70 against 143, 2048 of 3072 x 768
-// 22 against 25, 64 of 11008 x 4096 23 against 33 us.
+// the partial sums' traffic besides. Measured against the library's product, operands not in
+// the caches: 8192 rows of 11008 x 4096 581 against 785 us, 12608 of 3072 x 768 80 against 144,
+// 2000 of 3072 x 768 22 against 32, 64 of 11008 x 4096 24 against 34 us.
 #include "act_codes.hpp"
 #include "lmbp_device.hpp"
 #include "lmbp_launch.hpp"
@@ -438,18 +438,31 @@ hipError_t current_device(int& dev, int& cus) {
 }
 
 // Estimated time, in us, of a tile configuration with the rows split `splits` times: full
-// rounds of the resident blocks and a partial one, the partial sums' traffic, and for the
-// smaller tiles the operands beyond what the memory-side cache keeps. Least-squares fit
-// (7 to 10% rms) to measured times of M = 16 .. 12608 rows of five layers (512 x 2048, 768 x
-// 3072, 1024 x 4096, 2048 x 5632, 4096 x 11008), 1 to 12 splits, 256 CUs. The choice was
-// within 0.8% of the fastest on average, and 1.27 times the library's speed (0.77 to 2.0).
+// rounds of the resident blocks and a partial one (in which a CU with one block, and few CUs
+// with two, are faster), the partial sums' traffic and the second pass, the bytes of dW, dz and
+// x, and the operands beyond what the memory-side cache keeps. Non-negative least-squares fit
+// of the relative error, times near the size's best weighing more, to M = 1 .. 50000 rows of
+// 20 layers from 16 x 8 to 13824 x 5120, 1 to 32 splits, on 256 CUs (356 sizes). The choice is 0.6%
+// slower than the fastest plan on average and 13% at worst; with each layer's choices made
+// by a fit to the others, 0.6% and 13%. A fit to five layers, fewer terms and at most 12 splits
+// was 3.2% slower on average, 62% at worst: 6304 rows of 5120 x 1280 122 us against 99 (the
+// library's product: 108), 50000 of 64 x 64 43 against 27.5 (88). The library's product is
+// 1.47 times as slow on average; it is faster for the 16 x 8 layer from 197 to 4096 rows (by up
+// to 1.3 us of 5 to 10) and by 2 to 4% at four other sizes (4096 rows of 2048 x 5632 98 us).
 struct Cost {
-  float base, step_full, step_any, step_second, full, any, part_mb, split, out_mb, beyond_mb;
+  float base, step_full, step_any, step_second, full, any, part_mb, split, out_mb, beyond_mb, load_first, load_second,
+      dz_mb, x_mb, per_split, second, step_load, load, split_mb;
 };
-constexpr Cost kBigCost = {0.0f, 1.448f, 1.234f, 0.0f, 3.63f, 7.70f, 0.253f, 6.91f, 0.070f, 0.0f};
-constexpr Cost kMidCost = {1.15f, 1.468f, 0.786f, 0.511f, 0.10f, 3.95f, 0.304f, 5.06f, 0.163f, 0.138f};
-constexpr Cost kSmallCost = {3.90f, 0.812f, 0.511f, 0.216f, 0.0f, 0.0f, 0.317f, 4.41f, 0.181f, 0.338f};
+constexpr Cost kBigCost = {4.484f, 1.553f, 1.078f, 0, 3.471f, 0.567f, 0.2069f, 1.242f, 0.0496f, 0, 0.3734f, 0,
+                           0.03283f, 0.02745f, 0.2187f, 0, 0, 6.094f, 0.2307f};
+constexpr Cost kMidCost = {3.969f, 1.565f, 0.8659f, 0.3437f, 0, 0, 0.2849f, 1.272f, 0.138f, 0.01897f, 0.001652f,
+                           0.5249f, 0.03913f, 0.03597f, 0.2503f, 0.03601f, 0, 3.14f, 0.1684f};
+constexpr Cost kSmallCost = {3.511f, 0.9227f, 0.526f, 0.1757f, 0, 0, 0.2531f, 1.199f, 0.1548f, 0.02875f, 0, 0.2816f,
+                             0.08778f, 0.04232f, 0.2617f, 0, 0, 1.495f, 0.4445f};
 
+// The partial sums take at most 256 MiB, which no size that was measured asks for: 7 shares of
+// 3072 x 768 (12608 rows) are 66 MB, 4 of 5632 x 2048 (16384 rows) 185.
+constexpr int64_t kMaxSplits = 32, kMaxPartial = int64_t(256) << 20;
 struct Plan {
   int tile = 0;        // 0: 256 x 256, 1: 128 x 256, 2: 128 x 128
   int64_t splits = 1;  // shares of the rows that hold any
@@ -462,15 +475,20 @@ void consider(int tile, const Cost& c, int64_t M, int64_t N, int64_t K, int cus,
   const int64_t tiles = ((N + C::BM - 1) / C::BM) * ((K + C::BN - 1) / C::BN);
   const int64_t slots = int64_t(cus) * C::kBlocksPerCu;
   const float mb = float(N) * float(K) * 4e-6f;
-  const float beyond = std::max(0.0f, float(M) * float(N + K) * 2e-6f - 60.0f);
-  for (int64_t want = 1; want <= 12 && want <= steps; ++want) {
+  const float dz_mb = float(M) * float(N) * 2e-6f, x_mb = float(M) * float(K) * 2e-6f;
+  const float beyond = std::max(0.0f, dz_mb + x_mb - 60.0f);
+  for (int64_t want = 1; want <= kMaxSplits && want <= steps; ++want) {
     const int64_t per = (steps + want - 1) / want, splits = (steps + per - 1) / per;
     if (splits != want) continue;   // the same shares as a smaller number gives
-    const int64_t full = tiles * splits / slots, rest = tiles * splits % slots;
-    const float per_step = c.step_full * float(full) + c.step_any * float(rest > 0) + c.step_second * float(rest > cus);
-    const float t = c.base + per_step * float(per) + c.full * float(full) + c.any * float(rest > 0) +
-                    (splits > 1 ? c.part_mb * mb * float(splits) + c.split : 0.0f) + c.out_mb * mb * 0.5f +
-                    c.beyond_mb * beyond;
+    if (splits > 1 && splits * N * K * int64_t(sizeof(float)) > kMaxPartial) break;
+    const int64_t rest = tiles * splits % slots;
+    const float full = float(tiles * splits / slots), any = rest > 0, second = rest > cus;
+    const float per_cu = float(rest) / float(cus), load = float(rest) / float(slots);
+    const float per_step = c.step_full * full + c.step_any * any + c.step_second * second + c.step_load * load +
+                           (second > 0.0f ? c.load_second * (per_cu - 1.0f) : c.load_first * per_cu);
+    const float t = c.base + per_step * float(per) + c.full * full + c.any * any + c.second * second + c.load * load +
+                    (splits > 1 ? (c.part_mb * mb + c.per_split) * float(splits) + c.split + c.split_mb * mb : 0.0f) +
+                    c.out_mb * mb * 0.5f + c.beyond_mb * beyond + c.dz_mb * dz_mb + c.x_mb * x_mb;
     if (t < best) {
       best = t;
       plan = {tile, splits, per};
