@@ -46,7 +46,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-constexpr int kXcds = 8;
 constexpr int kRowsPerSlot = 32;
 
 // A block computes BM rows (output features) x BN columns (input features) of dW with WM x
@@ -420,23 +419,6 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restric
   *reinterpret_cast<u32x4*>(dw + i) = BF16::pack(v);
 }
 
-constexpr int kMaxDevices = 64;
-
-// CUs of the current device, queried once per device.
-hipError_t current_device(int& dev, int& cus) {
-  static std::atomic<int> known[kMaxDevices];
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  cus = known[dev].load(std::memory_order_relaxed);
-  if (cus == 0) {
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    known[dev].store(cus, std::memory_order_relaxed);
-  }
-  return hipSuccess;
-}
-
 // Estimated time, in us, of a tile configuration with the rows split `splits` times: full
 // rounds of the resident blocks and a partial one (in which a CU with one block, and few CUs
 // with two, are faster), the partial sums' traffic and the second pass, the bytes of dW, dz and
@@ -563,14 +545,14 @@ int64_t partial_floats(int64_t N, int64_t K, const Plan& p) { return p.splits > 
 
 size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias) {
   int dev = 0, cus = 256;
-  if (lgrad::current_device(dev, cus) != hipSuccess) cus = 256;   // a size to plan with, no device here
+  if (current_device(dev, cus) != hipSuccess) cus = 256;   // a size to plan with, no device here
   const lgrad::Plan plan = lgrad::make_plan(M, N, K, cus);
   return size_t(lgrad::partial_floats(N, K, plan) + (bias ? lgrad::col_plan(M, N).rows * N : 0)) * sizeof(float);
 }
 
 LinearGradForm linear_grad_form(int64_t M, int64_t N, int64_t K) {
   int dev = 0, cus = 256;
-  if (lgrad::current_device(dev, cus) != hipSuccess) cus = 256;   // no device here
+  if (current_device(dev, cus) != hipSuccess) cus = 256;   // no device here
   const lgrad::Plan plan = lgrad::make_plan(M, N, K, cus);
   auto rounds = [&](auto tile) {
     using C = decltype(tile);

@@ -80,7 +80,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int kXcds = 8;
 constexpr int kGroupM = 8;
 constexpr uint32_t kBufferGDword3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
 constexpr uint32_t kOutOfRange = 0x80000000u;    // beyond any resource's range: reads 0
@@ -634,23 +633,6 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void linear_act_fwd_rows_kernel
   if (a.z != nullptr) *reinterpret_cast<uint2*>(a.z + base) = z;
 }
 
-constexpr int kMaxDevices = 64;
-
-// The current device and its CU count (queried once per device).
-hipError_t current_device(int& dev, int& cus) {
-  static std::atomic<int> known[kMaxDevices];
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  cus = known[dev].load(std::memory_order_relaxed);
-  if (cus == 0) {
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    known[dev].store(cus, std::memory_order_relaxed);
-  }
-  return hipSuccess;
-}
-
 template <class C, bool GLU>
 constexpr int kOutCols = GLU ? C::BN / 2 : C::BN;   // output columns per tile
 
@@ -809,9 +791,23 @@ hipError_t launch_lin(const LinArgs& a, hipStream_t s) {
 
 }  // namespace lin
 
+hipError_t current_device(int& dev, int& cus) {
+  static std::atomic<int> known[kMaxDevices];
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  cus = known[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    known[dev].store(cus, std::memory_order_relaxed);
+  }
+  return hipSuccess;
+}
+
 LinearForm linear_form(bool gated, int64_t M, int64_t N, int64_t K) {
   int dev = 0, cus = 256;
-  if (lin::current_device(dev, cus) != hipSuccess) cus = 256;   // no device here
+  if (current_device(dev, cus) != hipSuccess) cus = 256;   // no device here
   lin::LinArgs a{};
   a.M = M;
   a.N = N;

@@ -9,6 +9,12 @@ namespace lmbp {
 
 enum { kGelu = 0, kSilu = 1 };
 
+constexpr int kXcds = 8;          // consecutive blocks go to them in turn
+constexpr int kMaxDevices = 64;   // of one process
+
+// The current device and its CU count (queried once per device).
+hipError_t current_device(int& dev, int& cus);
+
 // Runtime tables of a general family member (kernel argument, passed by value):
 // thresholds t[0..2^k-2] as fp32 round-down values, levels lv[0..2^k-1] in fp32.
 struct StepTable {

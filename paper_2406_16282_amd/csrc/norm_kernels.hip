@@ -363,8 +363,8 @@ __global__ __launch_bounds__(norm_block<WPR>()) void norm_fwd_pipe(const void* x
   }
 }
 
-// Block per row, any alignment and width (only widths beyond the register tile come here); each pass re-reads the row (from cache
-// for rows that fit).
+// Block per row, any alignment and width (widths beyond the register tile come here); each
+// pass re-reads the row (from cache for rows that fit).
 template <class IO, bool LN>
 __global__ __launch_bounds__(256) void norm_fwd_any(const void* x, void* z, float* __restrict__ rstd,
                                                     int64_t rows, int64_t cols, float eps) {
@@ -497,7 +497,6 @@ constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 // Any grid is correct; if the queries fail, one block per group.
 template <auto Kernel>
 int64_t persistent_grid(int block, int64_t groups) {
-  constexpr int kMaxDevices = 64;
   static std::atomic<int64_t> resident[kMaxDevices];
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= kMaxDevices) return groups;
