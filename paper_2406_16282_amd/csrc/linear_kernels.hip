@@ -664,16 +664,16 @@ hipError_t launch_tile(LinArgs a, int dev, int cus, hipStream_t s) {
 // CUs have it; K steps that are longer where rows do not begin on 128-byte lines; the
 // bytes of W, x and the outputs. The coefficients are non-negative least-squares fits of the
 // relative error (one set per configuration, plain and gated) to the times on 256 CUs of
-// M = 1 .. 16384 rows of 13 layers from 256 x 256 to 8192 x 1024 and 640 x 5120 with GELU, and of
-// M = 1 .. 4096 rows of 11 gated ones from 1024 x 1024 to 14336 x 4096: 377 and 308 sizes, inputs
-// and weights not in the caches, those near the size's best weighing more. The choice is 0.3%
-// (gated 0.4%) slower than the fastest form on average, 8% (10%) at worst; with each layer's choices
-// made by a fit to the other layers, 0.6% (0.8%), 21% (18%). A fit to fewer layers with fewer
-// terms was 4.3% (2.2%) slower on average, 48% (24%) at worst: 4096 rows of 256 x 256 10.1 us
+// M = 1 .. 16384 rows of 21 layers from 256 x 256 to 16384 x 4096 and 640 x 5120 with GELU, and of
+// M = 1 .. 4096 rows of 11 gated ones from 1024 x 1024 to 14336 x 4096: 577 and 308 sizes, gated
+// weights not in the caches, those near the size's best weighing more. The choice is 0.3%
+// (gated 0.4%) slower than the fastest form on average, 8% (10%) at worst; with each layer's
+// choices made by a fit to the other layers, 0.6% (0.8%), 21% (18%). A fit to fewer layers with
+// fewer terms was 4% (2%) slower on average, 48% (24%) at worst: 4096 rows of 256 x 256 10.1 us
 // against 7.7, 2500 of 4096 x 1024 41 against 32, 1500 of the gated 3072 x 768 34 against 26.
 struct Cost {
   float base, step_full, step_any, step_second, step_third, step_load, full, any, second, w_mb, out_mb, x_mb, w_full_mb,
-      step_ragged, load_second, load_third, load_first;
+      step_ragged, load_second, load_third, load_first, third;
 };
 template <class C, bool GLU>
 float cost(const LinArgs& a, int cus, const Cost& c) {
@@ -689,20 +689,20 @@ float cost(const LinArgs& a, int cus, const Cost& c) {
   const float per_step = c.step_full * full + c.step_any * any + c.step_second * second + c.step_third * third +
                          c.step_load * load + level + c.step_ragged * ragged * (full + load);
   return c.base + float((a.K + kBK - 1) / kBK) * per_step + c.full * full + c.any * any + c.second * second +
-         (c.w_mb + c.w_full_mb * full) * w_mb + c.out_mb * float(a.M) * float(a.N) * (GLU ? 6e-6f : 2e-6f) +
+         c.third * third + (c.w_mb + c.w_full_mb * full) * w_mb + c.out_mb * float(a.M) * float(a.N) * (GLU ? 6e-6f : 2e-6f) +
          c.x_mb * float(a.M) * float(a.K) * 2e-6f;
 }
 struct TileCosts {
   Cost big, mid, small, low;
 };
 constexpr TileCosts kLinearCost = {
-    {5.921f, 1.526f, 1.015f, 0, 0, 0.3973f, 7.993f, 7.732f, 0, 0, 0.1274f, 0.04803f, 0, 0.03257f, 0, 0, 0},
-    {8.992f, 1.649f, 0.6745f, 0.5608f, 0, 0, 4.083f, 1.508f, 1.367f, 0, 0.1426f, 0.03935f, 0.003606f, 0.2174f,
-     0.3989f, 0, 0.1587f},
-    {4.783f, 0.9873f, 0.4192f, 0.3014f, 0, 0, 1.069f, 0.549f, 0.878f, 0.005972f, 0.2383f, 0.0543f, 0, 0.2342f,
-     0.2733f, 0, 0.1053f},
-    {4.617f, 0.9295f, 0.3228f, 0.149f, 0.3207f, 0, 0.8561f, 0, 0.4019f, 0.008148f, 0.1836f, 0.07334f, 0, 0.3088f,
-     0.1102f, 0.1466f, 0.03835f}};
+    {6.259f, 1.45f, 0.9937f, 0, 0, 0.4028f, 8.674f, 7.53f, 0, 0, 0.1349f, 0.05882f, 0, 0.03813f, 0, 0, 0},
+    {9.257f, 1.56f, 0.6526f, 0.5393f, 0, 0, 5.355f, 1.417f, 1.664f, 0, 0.136f, 0.05564f, 0, 0.2322f, 0.4184f, 0,
+     0.1677f},
+    {4.851f, 0.9643f, 0.4103f, 0.2916f, 0, 0, 1.463f, 0.5558f, 1.205f, 0, 0.2253f, 0.0656f, 0, 0.2431f, 0.2573f,
+     0, 0.1185f},
+    {4.64f, 0.8936f, 0.3183f, 0.1567f, 0.302f, 0, 1.294f, 0, 0.3331f, 0.006352f, 0.1777f, 0.0818f, 0, 0.3159f,
+     0.1153f, 0.1076f, 0.04626f, 0.3873f}};
 constexpr TileCosts kGatedCost = {
     {5.759f, 1.485f, 0.955f, 0, 0, 0.6037f, 7.985f, 4.71f, 0, 0, 0.07038f, 0, 0, 0, 0, 0, 0},
     {7.16f, 1.561f, 0.7105f, 0.4801f, 0, 0, 6.558f, 0.4042f, 1.888f, 0.06568f, 0.08794f, 0, 0, 0.0264f, 0.598f, 0,
@@ -722,10 +722,10 @@ struct RowsCosts {
   RowsCost rows16, rows32;
 };
 constexpr RowsCosts kLinearRowsCost = {
-    {2.721f, 0.1513f, 0.01166f, 1.058f, 0, 0.7846f, 0.004431f, {0.1165f, 0.1443f, 0.1586f, 0, 0.2964f}, 0.233f,
-     0.9253f, 0.8186f},
-    {2.92f, 0.2037f, 0.00706f, 1.167f, 0, 0.5465f, 0.003384f, {0.1687f, 0.4693f, 0.1883f, 0, 0.5173f}, 0.4701f,
-     1.493f, 0.9763f}};
+    {2.732f, 0.1367f, 0.01947f, 0.415f, 0, 1.289f, 0.002784f, {0.08641f, 0.09539f, 0.1303f, 0, 0.1894f}, 0.221f,
+     0.7607f, 0.6995f},
+    {2.903f, 0.1851f, 0.01669f, 0, 0, 1.12f, 0.002581f, {0.1102f, 0.3399f, 0.06528f, 0, 0.2304f}, 0.4299f, 1.404f,
+     0.9115f}};
 constexpr RowsCosts kGatedRowsCost = {
     {2.568f, 0.1036f, 0.0152f, 0.749f, 0.1047f, 0.3545f, 0, {0.1776f, 0.1262f, 0.124f, 0, 0.1921f}, 0.387f,
      0.1411f, 0},

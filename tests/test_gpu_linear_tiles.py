@@ -52,11 +52,11 @@ GATED = [
 ROWS16, ROWS32, BIG, MID, SMALL, LOW = range(6)
 PLAIN_FORMS = [
     (ROWS16, (5, 64, 8)), (ROWS16, (23, 16, 8)), (ROWS16, (12, 16, 72)), (ROWS16, (31, 16, 88)),
-    (ROWS32, (19, 4320, 8)), (ROWS32, (4250, 16, 8)), (ROWS32, (17, 4272, 72)), (ROWS32, (315, 416, 72)),
-    (BIG, (3393, 2448, 840)), (BIG, (5021, 5136, 680)),
-    (MID, (8295, 9680, 8)), (MID, (2119, 3056, 1032)), (MID, (4147, 5152, 208)),
-    (SMALL, (2373, 944, 520)), (SMALL, (3877, 2064, 520)),
-    (LOW, (6842, 80, 8)), (LOW, (8316, 656, 16)), (LOW, (2926, 208, 72)), (LOW, (8235, 656, 72)),
+    (ROWS32, (19, 4320, 8)), (ROWS32, (4597, 16, 8)), (ROWS32, (17, 4272, 72)), (ROWS32, (315, 416, 72)),
+    (BIG, (3851, 2208, 840)), (BIG, (5021, 5136, 680)),
+    (MID, (8266, 10976, 8)), (MID, (2436, 2736, 1032)), (MID, (4384, 4768, 264)),
+    (SMALL, (1735, 1424, 520)), (SMALL, (3879, 2112, 464)),
+    (LOW, (166, 4256, 8)), (LOW, (8316, 656, 16)), (LOW, (1158, 688, 72)), (LOW, (8235, 656, 72)),
 ]
 GATED_FORMS = [
     (ROWS16, (6, 16, 24)), (ROWS16, (32, 16, 8)), (ROWS16, (1, 16, 72)), (ROWS16, (36, 16, 72)),
