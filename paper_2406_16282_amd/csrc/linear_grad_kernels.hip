@@ -445,11 +445,7 @@ constexpr Cost kSmallCost = {3.511f, 0.9227f, 0.526f, 0.1757f, 0, 0, 0.2531f, 1.
 // The partial sums take at most 256 MiB, which no size that was measured asks for: 7 shares of
 // 3072 x 768 (12608 rows) are 66 MB, 4 of 5632 x 2048 (16384 rows) 185.
 constexpr int64_t kMaxSplits = 32, kMaxPartial = int64_t(256) << 20;
-struct Plan {
-  int tile = 0;        // 0: 256 x 256, 1: 128 x 256, 2: 128 x 128
-  int64_t splits = 1;  // shares of the rows that hold any
-  int64_t per = 1;     // 64-row steps per share
-};
+using Plan = LinearGradPlan;
 
 template <class C>
 void consider(int tile, const Cost& c, int64_t M, int64_t N, int64_t K, int cus, float& best, Plan& plan) {
@@ -459,7 +455,7 @@ void consider(int tile, const Cost& c, int64_t M, int64_t N, int64_t K, int cus,
   const float mb = float(N) * float(K) * 4e-6f;
   const float dz_mb = float(M) * float(N) * 2e-6f, x_mb = float(M) * float(K) * 2e-6f;
   const float beyond = std::max(0.0f, dz_mb + x_mb - 60.0f);
-  for (int64_t want = 1; want <= kMaxSplits && want <= steps; ++want) {
+  for (int64_t want = 1; want <= kMaxSplits && want <= steps; want += want < 12 ? 1 : 4) {
     const int64_t per = (steps + want - 1) / want, splits = (steps + per - 1) / per;
     if (splits != want) continue;   // the same shares as a smaller number gives
     if (splits > 1 && splits * N * K * int64_t(sizeof(float)) > kMaxPartial) break;
@@ -543,10 +539,13 @@ int64_t partial_floats(int64_t N, int64_t K, const Plan& p) { return p.splits > 
 
 }  // namespace lgrad
 
-size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias) {
+LinearGradPlan linear_grad_plan(int64_t M, int64_t N, int64_t K) {
   int dev = 0, cus = 256;
   if (current_device(dev, cus) != hipSuccess) cus = 256;   // a size to plan with, no device here
-  const lgrad::Plan plan = lgrad::make_plan(M, N, K, cus);
+  return lgrad::make_plan(M, N, K, cus);
+}
+
+size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias, const LinearGradPlan& plan) {
   return size_t(lgrad::partial_floats(N, K, plan) + (bias ? lgrad::col_plan(M, N).rows * N : 0)) * sizeof(float);
 }
 
@@ -565,12 +564,12 @@ LinearGradForm linear_grad_form(int64_t M, int64_t N, int64_t K) {
 }
 
 hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const void* dy, const uint32_t* codes,
-                              const void* x, void* dz, void* dw, void* db, void* workspace, hipStream_t s) {
+                              const void* x, void* dz, void* dw, void* db, void* workspace,
+                              const LinearGradPlan& plan, hipStream_t s) {
   using namespace lgrad;
   int dev = 0, cus = 0;
   hipError_t e = current_device(dev, cus);
   if (e != hipSuccess) return e;
-  const Plan plan = make_plan(M, N, K, cus);
   float* const part = static_cast<float*>(workspace);
   float* const sums = part + (dw != nullptr ? partial_floats(N, K, plan) : 0);
   const ColPlan cols = col_plan(M, N);

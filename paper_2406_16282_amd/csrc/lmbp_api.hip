@@ -318,7 +318,9 @@ lmbp_status linear_grad_impl(bool with_act, lmbp_act act, lmbp_dtype dt, int64_t
   for (const void* p : sixteen)
     if (p && !aligned(p, 16)) return LMBP_EINVAL;
   if ((db && !aligned(db, 2)) || (codes && !aligned(codes, 4))) return LMBP_EINVAL;
-  const uint64_t need = lmbp::linear_grad_workspace(m, n, grad ? k : 0, db != nullptr);   // no dw: no partial sums
+  const int64_t kw = grad ? k : 0;   // no dw: no partial sums
+  const lmbp::LinearGradPlan plan = lmbp::linear_grad_plan(m, n, kw);
+  const uint64_t need = lmbp::linear_grad_workspace(m, n, kw, db != nullptr, plan);
   if (need > 0 && (!workspace || workspace_bytes < 0 || uint64_t(workspace_bytes) < need)) return LMBP_EINVAL;
   const uint64_t mn = uint64_t(m) * uint64_t(n) * 2, mk = uint64_t(m) * uint64_t(k) * 2;
   const Span sdw = span(dw, grad ? uint64_t(n) * uint64_t(k) * 2 : 0);
@@ -339,7 +341,7 @@ lmbp_status linear_grad_impl(bool with_act, lmbp_act act, lmbp_dtype dt, int64_t
     if (e != hipSuccess) return from_hip(e);
   }
   return from_hip(lmbp::launch_linear_grad(a, m, n, k, dy, codes, x, const_cast<void*>(dz),
-                                           grad ? dw : nullptr, db, workspace,
+                                           grad ? dw : nullptr, db, workspace, plan,
                                            static_cast<hipStream_t>(stream)));
 }
 
@@ -491,7 +493,7 @@ int lmbp_linear_grad_form(int64_t m, int64_t n, int64_t k, int64_t* splits, int6
 }
 size_t lmbp_linear_grad_bytes(int64_t m, int64_t n, int64_t k, int bias) {
   if (m < 0 || n <= 0 || k < 0 || n > (int64_t(1) << 24) || k > (int64_t(1) << 24)) return 0;
-  return lmbp::linear_grad_workspace(m, n, k, bias != 0);
+  return lmbp::linear_grad_workspace(m, n, k, bias != 0, lmbp::linear_grad_plan(m, n, k));
 }
 lmbp_status linear_weight_grad(lmbp_dtype dt, int64_t m, int64_t n, int64_t k, const void* dz,
                                const void* x, void* dw, void* workspace, int64_t workspace_bytes,

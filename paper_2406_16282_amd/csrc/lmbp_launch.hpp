@@ -82,11 +82,15 @@ struct LinearForm {
 };
 LinearForm linear_form(bool gated, int64_t M, int64_t N, int64_t K);
 
-// Backward of a fused linear layer's parameters. db non-null: dz = dy slope[code] is
-// computed here (act) and db is the column sums of dz; else dz is an input. dw non-null:
-// dw = bf16(dz^T x). Workspace of linear_grad_workspace bytes (of the same sizes; bias: db
-// non-null; K = 0 if dw is null). N % 16 == 0, K % 8 == 0, every tensor 16-byte aligned, db 2-byte aligned.
-size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias);
+// How dW is computed on the current device (256 CUs without one): made once per call, for K =
+// 0 if dw is not asked for.
+struct LinearGradPlan {
+  int tile = 0;        // 0: 256 x 256, 1: 128 x 256, 2: 128 x 128
+  int64_t splits = 1;  // shares of the rows that hold any
+  int64_t per = 1;     // 64-row steps per share
+};
+LinearGradPlan linear_grad_plan(int64_t M, int64_t N, int64_t K);
+size_t linear_grad_workspace(int64_t M, int64_t N, int64_t K, bool bias, const LinearGradPlan& plan);
 // The tile of dW (0 .. 2: 256 x 256, 128 x 256, 128 x 128), the shares that its rows are split
 // into, and the most units of work that a block takes.
 struct LinearGradForm {
@@ -94,8 +98,15 @@ struct LinearGradForm {
   int64_t splits, rounds;
 };
 LinearGradForm linear_grad_form(int64_t M, int64_t N, int64_t K);
+
+// Backward of a fused linear layer's parameters. db non-null: dz = dy slope[code] is
+// computed here (act) and db is the column sums of dz; else dz is an input. dw non-null:
+// dw = bf16(dz^T x). Workspace of linear_grad_workspace bytes (same sizes and plan; bias: db
+// non-null; K = 0 if dw is null). N % 16 == 0, K % 8 == 0, every tensor 16-byte aligned, db 2-byte
+// aligned.
 hipError_t launch_linear_grad(int act, int64_t M, int64_t N, int64_t K, const void* dy, const uint32_t* codes,
-                              const void* x, void* dz, void* dw, void* db, void* workspace, hipStream_t s);
+                              const void* x, void* dz, void* dw, void* db, void* workspace,
+                              const LinearGradPlan& plan, hipStream_t s);
 
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t s);
 
