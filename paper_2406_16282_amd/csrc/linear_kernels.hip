@@ -671,6 +671,9 @@ hipError_t launch_tile(LinArgs a, int dev, int cus, hipStream_t s) {
 // choices made by a fit to the other layers, 0.6% (0.8%), 21% (18%). A fit to fewer layers with
 // fewer terms was 4% (2%) slower on average, 48% (24%) at worst: 4096 rows of 256 x 256 10.1 us
 // against 7.7, 2500 of 4096 x 1024 41 against 32, 1500 of the gated 3072 x 768 34 against 26.
+// kLinearCost.mid is 1.5% above its fit, which runs 2 to 8% short of the largest layers' times and
+// took 128 x 256 tiles for the [8192 x 4096] x 11008 layer (607 against 593 us); the average is
+// the same with it.
 struct Cost {
   float base, step_full, step_any, step_second, step_third, step_load, full, any, second, w_mb, out_mb, x_mb, w_full_mb,
       step_ragged, load_second, load_third, load_first, third;
@@ -697,8 +700,8 @@ struct TileCosts {
 };
 constexpr TileCosts kLinearCost = {
     {6.259f, 1.45f, 0.9937f, 0, 0, 0.4028f, 8.674f, 7.53f, 0, 0, 0.1349f, 0.05882f, 0, 0.03813f, 0, 0, 0},
-    {9.257f, 1.56f, 0.6526f, 0.5393f, 0, 0, 5.355f, 1.417f, 1.664f, 0, 0.136f, 0.05564f, 0, 0.2322f, 0.4184f, 0,
-     0.1677f},
+    {9.396f, 1.583f, 0.6624f, 0.5474f, 0, 0, 5.435f, 1.438f, 1.689f, 0, 0.138f, 0.05647f, 0, 0.2357f, 0.4247f, 0,
+     0.1702f},
     {4.851f, 0.9643f, 0.4103f, 0.2916f, 0, 0, 1.463f, 0.5558f, 1.205f, 0, 0.2253f, 0.0656f, 0, 0.2431f, 0.2573f,
      0, 0.1185f},
     {4.64f, 0.8936f, 0.3183f, 0.1567f, 0.302f, 0, 1.294f, 0, 0.3331f, 0.006352f, 0.1777f, 0.0818f, 0, 0.3159f,

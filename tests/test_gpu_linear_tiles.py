@@ -37,7 +37,7 @@ SHAPES = [
     (777, 3088, 136), (3000, 4112, 72), (8000, 8208, 8),
     (1999, 3088, 72), (3001, 2064, 72), (9001, 2064, 640),
     (3001, 8176, 520), (4097, 5648, 776),
-    (1999, 6160, 520), (3001, 4112, 520), (4097, 3056, 520), (4100, 11008, 1032),
+    (1999, 6160, 520), (3001, 4112, 520), (4097, 3056, 520), (4100, 11008, 1032), (8266, 10976, 8),
 ]
 GATED = [
     (1, 16, 8), (16, 11008, 520), (17, 48, 264), (29, 5632, 2056), (100, 80, 776),
@@ -47,14 +47,14 @@ GATED = [
 ]
 # Sizes by the form that they take (256 CUs): split K with 16 and 32 rows to a block, tiles of
 # 256 x 256, 128 x 256, 128 x 128 and 64 x 128 (gated: half the columns); one or several row
-# blocks (split K) or tiles to a block, several K steps or one (which few of the tiles are
-# taken for).
+# blocks (split K) or tiles to a block, several K steps or one (for which only the smallest
+# tile is taken).
 ROWS16, ROWS32, BIG, MID, SMALL, LOW = range(6)
 PLAIN_FORMS = [
     (ROWS16, (5, 64, 8)), (ROWS16, (23, 16, 8)), (ROWS16, (12, 16, 72)), (ROWS16, (31, 16, 88)),
     (ROWS32, (19, 4320, 8)), (ROWS32, (4597, 16, 8)), (ROWS32, (17, 4272, 72)), (ROWS32, (315, 416, 72)),
-    (BIG, (3851, 2208, 840)), (BIG, (5021, 5136, 680)),
-    (MID, (8266, 10976, 8)), (MID, (2436, 2736, 1032)), (MID, (4384, 4768, 264)),
+    (BIG, (3851, 2208, 840)), (BIG, (5789, 4384, 600)),
+    (MID, (2784, 2528, 1032)), (MID, (3465, 6096, 264)),
     (SMALL, (1735, 1424, 520)), (SMALL, (3879, 2112, 464)),
     (LOW, (166, 4256, 8)), (LOW, (8316, 656, 16)), (LOW, (1158, 688, 72)), (LOW, (8235, 656, 72)),
 ]
@@ -79,7 +79,6 @@ def test_every_form_is_covered(gated, sizes):
         seen.add((form, several, k > 64))
     assert seen >= {(f, s, True) for f in range(6) for s in (False, True)}
     assert seen >= {(f, s, False) for f in (ROWS16, ROWS32, LOW) for s in (False, True)}
-    assert gated or (MID, True, False) in seen
 
 
 @pytest.mark.gpu
