@@ -18,9 +18,11 @@
 // busy 70% of the cycles; the ring below (half steps, loads spread over the MFMAs, two
 // to three half steps in flight) gave 597 us, the persistent blocks with the epilogue in
 // registers 581 us; the gated [8192 x 4096] x 2 [4096 x 11008] layer went from 1213 to
-// 1113 us. Products with a short K (ViT-B: 768): the epilogue, about 22 VALU operations
-// per element, is as long as the K loop; two blocks per CU let one block's epilogue run
-// beside the other's MFMAs (78 us, against 83-86 us for either of the other tiles).
+// 1113 us (same card; others run 2 to 8% slower). No address spilled in the epilogue gave 1 to
+// 2% more there and 4 to 8% at smaller sizes. Products with a short K (ViT-B: 768): the epilogue,
+// about 22 VALU operations per element, is as long as the K loop; two blocks per CU let one
+// block's epilogue run beside the other's MFMAs (77 us in 128 x 256 tiles, two to a CU, against
+// 88 in 128 x 128 and 91 in 256 x 256, one to a CU).
 //
 // Tiling. A block computes a BM x BN tile of z with WM x WN waves, each BM/WM x 64 as
 // 16 x 16 MFMA tiles, accumulators in registers. Four tiles are compiled, and a
