@@ -321,3 +321,12 @@ def test_gradient_errors(L):
 def test_form_queries(L):
     assert L.lmbp_linear_form(0, 16, 8, 0, None) == L.lmbp_linear_form(16, 0, 8, 1, None) == -1
     assert L.lmbp_linear_grad_form(5, 16, 0, None, None) == -1 and L.lmbp_linear_grad_form(0, 16, 8, None, None) >= 0
+
+
+def test_no_kernel_spills_registers(L):
+    """The code objects' notes in the built library: no register of any kernel in scratch (the
+    large GEMM tiles use all that there are, and a reload there waits for all loads and stores)."""
+    data = open(B.LIB_PATH, "rb").read()
+    for key in (b".vgpr_spill_count", b".sgpr_spill_count", b".private_segment_fixed_size"):
+        values = [data[m.end()] for m in re.finditer(re.escape(key), data)]   # msgpack: 0 is the byte 0
+        assert len(values) > 200 and not any(values), key
